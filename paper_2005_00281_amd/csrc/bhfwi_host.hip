@@ -152,6 +152,7 @@ struct TileSet {
 
 struct bhfwi_ctx {
     int device = 0;
+    int ncu = 256;  // compute units of the device
     int nshot = 0;
     int64_t model_len = 0;
     int ckpt_every = 0;
@@ -333,6 +334,33 @@ void build_tiles(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Sh
             }
         }
     }
+    // All tiles in one launch of the PML kernel (it takes any tile) where they
+    // fit the GPU in one round of workgroups, one per compute unit: the
+    // interior and the PML launch would each leave most of the GPU idle and run
+    // one after the other.  One shot of 148 x 552 cells, 1000 steps, gradient
+    // with checkpoints, 6x32x16 tiles: 13.75 ms in two launches per block, 7.56
+    // ms in one; beyond one round the interior kernel's second workgroup per
+    // compute unit is worth more (340 x 2088 cells, 8x32x16: 19.6 ms against
+    // 20.9 ms).
+    if (sh.T == pml.T && sh.TRE == pml.TRE && sh.W == pml.W && !ts->t[0].empty() &&
+        (int)(ts->t[0].size() + ts->t[1].size()) <= c->ncu) {
+        std::vector<std::pair<int, int4>> all;
+        for (int q = 0; q < 2; ++q)
+            for (size_t j = 0; j < ts->t[q].size(); ++j)
+                all.push_back({ts->nt[q][j], ts->t[q][j]});
+        std::stable_sort(all.begin(), all.end(),
+                         [](const std::pair<int, int4>& a, const std::pair<int, int4>& b) {
+                             return a.first > b.first;
+                         });
+        for (int q = 0; q < 2; ++q) {
+            ts->t[q].clear();
+            ts->nt[q].clear();
+        }
+        for (const auto& a : all) {
+            ts->t[1].push_back(a.second);
+            ts->nt[1].push_back(a.first);
+        }
+    }
 }
 
 int upload_tiles(bhfwi_ctx* c, TileSet* ts)
@@ -402,6 +430,43 @@ int default_rows(const bhfwi_ctx* c)
         strip_rows += (int64_t)((S.NZ + bhfwi::kOwn - 1) / bhfwi::kOwn) * S.NR;
     int64_t r = strip_rows / 8192;
     return (int)std::max<int64_t>(4, std::min<int64_t>(64, r));
+}
+
+// Tiles of the temporally blocked shape (T, TRE, .) over every shot.
+int64_t count_tiles(const bhfwi_ctx* c, int T, int TRE)
+{
+    int64_t n = 0;
+    for (const ShotDev& S : c->sd)
+        n += (int64_t)((S.NZ + 63 - 2 * T) / (64 - 2 * T)) *
+             ((S.NR + TRE - 2 * T - 1) / (TRE - 2 * T));
+    return n;
+}
+
+// Kernel shapes of a survey whose tune was never set (bhfwi_autotune refines
+// them).  The adjoint runs 6x32x16: its correlation sums are regrouped by the
+// steps of a block.
+// The forward takes eight steps; its rows were chosen on single and batched
+// gradients (ms, against 6x32x16 in both directions):
+//   tiles that fit the GPU in one round run in one launch per block, on 32 rows
+//     (148 x 552 cells, 1000 steps: 6.9 against 13.7) or 48 (220 x 1540, 400
+//     steps: 4.9 against 6.5);
+//   one and a half rounds of 64-row tiles, whose interior ones fit in one
+//     (340 x 2088, 400 steps: 7.5 against 8.7);
+//   the rest: 48 rows (2 shots of 276 x 4136: 16.9 against 18.0).
+void default_shapes(bhfwi_ctx* c)
+{
+    bhfwi_tune& t = c->tune;
+    t.tb_steps = 8;
+    t.tb_waves = 16;
+    t.adj_tb_steps = 6;
+    t.adj_tb_rows = 32;
+    t.adj_tb_waves = 16;
+    if (count_tiles(c, 8, 32) <= c->ncu)
+        t.tb_rows = 32;
+    else if (count_tiles(c, 8, 48) <= c->ncu)
+        t.tb_rows = 48;
+    else
+        t.tb_rows = 2 * count_tiles(c, 8, 64) <= 3 * (int64_t)c->ncu ? 64 : 48;
 }
 
 int active_items(const bhfwi_ctx* c, int n)
@@ -718,7 +783,7 @@ struct PmlFork {
 #define BHFWI_TB(TT, RR, WW)                                                                 \
     if (T == TT && TRE == RR && W == WW) {                                                   \
         hipLaunchKernelGGL((bhfwi::k_fwd_tb<TT, RR, WW, PMV>), dim3(nact), dim3(64 * WW), 0, \
-                           fork.stream(q), c->d_shots, c->ftiles.d[q], nact,                 \
+                           fork.stream(q), c->d_shots, ts.d[q], nact,                        \
                            c->tune.tile_map, n0,                                             \
                            nsteps, lam, mu, rho, wav, c->d_rec, c->d_pml_r, c->d_pml_z, in,  \
                            out, traces, hist, (long long)(2 * c->cells),                    \
@@ -732,14 +797,15 @@ void fwd_tb_launch(bhfwi_ctx* c, hipStream_t st, int n0, int nsteps, const float
                    const float* mu, const float* rho, const float* wav, const float* in,
                    float* out, float* traces, float* hist)
 {
-    const int na[2] = {active_tiles(c->ftiles, 0, n0), active_tiles(c->ftiles, 1, n0)};
+    const TileSet& ts = c->ftiles;
+    const int na[2] = {active_tiles(ts, 0, n0), active_tiles(ts, 1, n0)};
     if (na[0] + na[1] <= 0) return;
     EvScope ev(c, st, hist ? 1 : 0);
     PmlFork fork(c, st, na);
     for (int q = 0; q < 2; ++q) {
         const int nact = na[q];
         if (nact <= 0) continue;
-        const Shape sh = q ? c->ftiles.pml : fwd_shape(c);
+        const Shape sh = q ? ts.pml : fwd_shape(c);
         const int T = sh.T, TRE = sh.TRE, W = sh.W;
         if (q == 0) {
             constexpr int PMV = 0;
@@ -967,6 +1033,12 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
         (nrec_total > 0 && !rec_k))
         return bail(fail(c, BHFWI_EINVAL, "bad survey arguments"));
     c->device = hip_device;
+    if (hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, hip_device) !=
+            hipSuccess ||
+        c->ncu < 1) {
+        (void)hipGetLastError();
+        c->ncu = 256;
+    }
     c->nshot = nshot;
     c->model_len = model_len;
     c->ckpt_every = ckpt_every;
@@ -1087,9 +1159,7 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
     c->tune.waves_per_block = 4;
     c->tune.use_graph = 1;
     c->tune.time_kernels = 0;
-    c->tune.tb_steps = 6;  // measured best on single and batched shots; bhfwi_autotune refines
-    c->tune.tb_rows = 32;
-    c->tune.tb_waves = 16;
+    default_shapes(c);
     c->tune.tile_map = 1;
     c->tune.pml_overlap = 0;  // measured: concurrent PML tiles crowd out interior ones
     c->tune.fwd_tile_overlap = 0;
@@ -1117,7 +1187,6 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
     CREATE_HIP(hipMemset(c->d_status, 0, sizeof(int)));
 #undef CREATE_HIP
     if (int rc = upload_work(c)) return bail(rc);
-    *out = c;
     return BHFWI_OK;
 }
 
