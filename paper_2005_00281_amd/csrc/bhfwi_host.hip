@@ -4,6 +4,8 @@
 #include "bhfwi_kernels.hip"
 #include "bhfwi_tb_fwd.hip"
 #include "bhfwi_tb_adj.hip"
+#include "bhfwi_march_fwd.hip"
+#include "bhfwi_march_adj.hip"
 #include "bhfwi_o4.hip"
 #include "bhfwi_o4_tb.hip"
 
@@ -171,6 +173,7 @@ struct bhfwi_ctx {
     std::vector<int> work_nt;  // nt of each work item's shot, non-increasing
     TileSet ftiles, atiles;    // temporally blocked tiles of the forward / adjoint shape
     TileSet xtiles;            // the adjoint's with extra outputs, when they differ
+    TileSet fmarch, amarch;    // tiles of the marches (list 0) and the PML tiles beside them
     ShotDev* d_shots = nullptr;
     int* d_rec = nullptr;
     float* d_pml_r = nullptr;
@@ -363,6 +366,92 @@ void build_tiles(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Sh
     }
 }
 
+// Columns of 64 - 2T axial rows of shot S that are clear of the axial PML.
+int clear_columns(const ShotDev& S, int T)
+{
+    int n = 0;
+    for (int k0 = 0; k0 < S.NZ; k0 += 64 - 2 * T)
+        n += k0 - T >= S.pz && k0 - T + 63 < S.NZ - S.pz;
+    return n;
+}
+
+// Radial rows per tile of the march kernels with T steps per launch, or 0
+// where the LDS tiles run.  A wave issues a vector instruction every other
+// slot of its SIMD, so the marches need two waves per SIMD (8 per compute
+// unit) to keep the GPU busy, and a tile of R rows takes R + 2T march steps:
+// R minimises the number of rounds of that many waves times R + 2T.  Below 64
+// rows the fill (2T of R + 2T steps) costs more than the LDS tiles' halo, and
+// a survey that needs shorter tiles to fill the GPU keeps the LDS tiles
+// (measured, gradient of 400 steps: 4 shots of 276 x 4136 cells 31.3 ms in LDS
+// tiles, 34.5 ms in 48-row marches; 8 shots 63.9 against 55.5 ms in 84-row
+// marches).  Planes and model windows are addressed by 32-bit byte offsets.
+int march_rows(const bhfwi_ctx* c, int T)
+{
+    if (!(T == 4 || T == 6 || T == 8)) return 0;
+    const int64_t lim = (int64_t)1 << 31;
+    for (const ShotDev& S : c->sd)
+        if (4 * (int64_t)S.NR * S.NZ >= lim ||
+            4 * ((int64_t)(S.NR - 1) * S.model_ld + S.NZ) >= lim)
+            return 0;
+    std::vector<std::pair<int, int>> cols;  // (clear columns, rows in them) per shot
+    int most = 0;
+    for (const ShotDev& S : c->sd) {
+        const int top = S.nr - T;
+        if (top < 1) continue;
+        cols.push_back({clear_columns(S, T), top});
+        most = std::max(most, top);
+    }
+    const int64_t slots = 8 * (int64_t)c->ncu;
+    int best = 0;
+    int64_t best_t = 0;
+    for (int R = 64; R <= std::min(320, (most + 3) / 4 * 4); R += 4) {
+        int64_t n = 0;
+        for (const auto& q : cols) n += (int64_t)q.first * ((q.second + R - 1) / R);
+        const int64_t t = (n + slots - 1) / slots * (R + 2 * T);
+        if (n < slots - slots / 8) break;  // longer tiles leave still fewer waves
+        if (!best || t <= best_t) {
+            best = R;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+// Tiles of the march kernels with T steps per launch.  In a column clear of
+// the axial PML, the rows whose skewed window stays below the radial layer are
+// cut into equal tiles of at most R rows (list 0: shot, first owned axial row,
+// radial rows [z, w)); the rest of the column, and every column that reaches
+// an axial layer, into the LDS tiles of shape pml (list 1).
+void build_march(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Shape pml,
+                 TileSet* ts)
+{
+    for (int q = 0; q < 2; ++q) {
+        ts->t[q].clear();
+        ts->nt[q].clear();
+    }
+    ts->pml = pml;
+    const int T = sh.T, R = march_rows(c, T);
+    if (R < 1) return;
+    const int TZ = 64 - 2 * T, TRp = pml.TRE - 2 * T;
+    for (int s : order) {
+        const ShotDev& S = c->sd[s];
+        for (int k0 = 0; k0 < S.NZ; k0 += TZ) {
+            const bool clear = k0 - T >= S.pz && k0 - T + 63 < S.NZ - S.pz;
+            const int top = clear ? std::max(0, S.nr - T) : 0;
+            const int n = (top + R - 1) / R;
+            for (int j = 0; j < n; ++j) {
+                ts->t[0].push_back(make_int4(s, k0, (int)((int64_t)top * j / n),
+                                             (int)((int64_t)top * (j + 1) / n)));
+                ts->nt[0].push_back(S.nt);
+            }
+            for (int i0 = top; i0 < S.NR; i0 += TRp) {
+                ts->t[1].push_back(make_int4(s, k0, i0, i0));
+                ts->nt[1].push_back(S.nt);
+            }
+        }
+    }
+}
+
 int upload_tiles(bhfwi_ctx* c, TileSet* ts)
 {
     for (int q = 0; q < 2; ++q) {
@@ -401,6 +490,8 @@ void rebuild_work(bhfwi_ctx* c)
     build_tiles(c, order, fs, pml_shape(fs, false), &c->ftiles, c->tune.fwd_tile_overlap != 0);
     build_tiles(c, order, as, pml_shape(as, true), &c->atiles);
     build_tiles(c, order, xs, pml_shape(xs, true), &c->xtiles);
+    build_march(c, order, fs, pml_shape(fs, false), &c->fmarch);
+    build_march(c, order, as, pml_shape(as, true), &c->amarch);
     // fourth-order forward blocks: a three-cell halo per step, one shape for
     // the interior and the PML tiles
     const Shape h4{3 * c->f4.T, c->f4.TRE, c->f4.W};
@@ -419,6 +510,8 @@ int upload_work(bhfwi_ctx* c)
     if (int rc = upload_tiles(c, &c->ftiles)) return rc;
     if (int rc = upload_tiles(c, &c->atiles)) return rc;
     if (int rc = upload_tiles(c, &c->f4tiles)) return rc;
+    if (int rc = upload_tiles(c, &c->fmarch)) return rc;
+    if (int rc = upload_tiles(c, &c->amarch)) return rc;
     return upload_tiles(c, &c->xtiles);
 }
 
@@ -444,12 +537,15 @@ int64_t count_tiles(const bhfwi_ctx* c, int T, int TRE)
 
 // Kernel shapes of a survey whose tune was never set (bhfwi_autotune refines
 // them).  The adjoint runs 6x32x16: its correlation sums are regrouped by the
-// steps of a block.
+// steps of a block, and eight steps are no faster where they matter (12 shots
+// of 276 x 4136 cells: 85.4 ms with six, 93.5 with eight, whose marches spill).
 // The forward takes eight steps; its rows were chosen on single and batched
 // gradients (ms, against 6x32x16 in both directions):
 //   tiles that fit the GPU in one round run in one launch per block, on 32 rows
 //     (148 x 552 cells, 1000 steps: 6.9 against 13.7) or 48 (220 x 1540, 400
 //     steps: 4.9 against 6.5);
+//   enough columns for the marches: 48-row PML tiles (8 shots of 276 x 4136,
+//     400 steps: 59.5 against 70.0);
 //   one and a half rounds of 64-row tiles, whose interior ones fit in one
 //     (340 x 2088, 400 steps: 7.5 against 8.7);
 //   the rest: 48 rows (2 shots of 276 x 4136: 16.9 against 18.0).
@@ -463,7 +559,7 @@ void default_shapes(bhfwi_ctx* c)
     t.adj_tb_waves = 16;
     if (count_tiles(c, 8, 32) <= c->ncu)
         t.tb_rows = 32;
-    else if (count_tiles(c, 8, 48) <= c->ncu)
+    else if (count_tiles(c, 8, 48) <= c->ncu || march_rows(c, 8))
         t.tb_rows = 48;
     else
         t.tb_rows = 2 * count_tiles(c, 8, 64) <= 3 * (int64_t)c->ncu ? 64 : 48;
@@ -757,9 +853,10 @@ struct PmlFork {
     bhfwi_ctx* c;
     hipStream_t st;
     bool on = false;
-    PmlFork(bhfwi_ctx* c_, hipStream_t st_, const int na[2]) : c(c_), st(st_)
+    PmlFork(bhfwi_ctx* c_, hipStream_t st_, const int na[2], bool march = false) : c(c_), st(st_)
     {
-        if (!c->tune.pml_overlap || na[0] <= 0 || na[1] <= 0) return;
+        if (!(c->tune.pml_overlap || (march && !c->tune.rec_overlap)) || na[0] <= 0 || na[1] <= 0)
+            return;
         if (!c->pml_stream &&
             hipStreamCreateWithFlags(&c->pml_stream, hipStreamNonBlocking) != hipSuccess)
             return;
@@ -780,6 +877,61 @@ struct PmlFork {
     }
 };
 
+// Steps per launch of the march kernels (a remainder of a block runs the
+// kernel of its own length on the same tiles).
+#define BHFWI_MARCH(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+
+// The nsteps (<= T) steps from step n0 of a block on its interior tiles (na of
+// them in ts), by the forward march.
+void fwd_march_launch(bhfwi_ctx* c, hipStream_t st, const TileSet& ts, int na, int n0, int nsteps,
+                      const float* lam, const float* mu, const float* rho, const float* wav,
+                      const float* in, float* out, float* traces, float* hist)
+{
+    const int tz = 64 - 2 * c->tune.tb_steps;
+#define BHFWI_MF(TT, HH)                                                                      \
+    hipLaunchKernelGGL((bhfwi::march::k_fwd_march<TT, HH>), dim3(na), dim3(64), 0, st,        \
+                       c->d_shots, ts.d[0], na, c->tune.tile_map, tz, n0, lam, mu, rho, wav,  \
+                       c->d_rec, c->d_pml_r, in, out, traces, hist,                           \
+                       (long long)(2 * c->cells), (long long)c->cells)
+#define BHFWI_ML(TT)                  \
+    case TT:                          \
+        if (hist) BHFWI_MF(TT, 1);    \
+        else BHFWI_MF(TT, 0);         \
+        break;
+    switch (nsteps) { BHFWI_MARCH(BHFWI_ML) }
+#undef BHFWI_ML
+#undef BHFWI_MF
+}
+
+// Adjoint steps n_hi, n_hi - 1, ... (nsteps of them) of a block on its
+// interior tiles, by the adjoint march; xm as in launch_adj_tb.
+void adj_march_launch(bhfwi_ctx* c, hipStream_t st, const TileSet& ts, int na, int T, int n_hi,
+                      int nsteps, const float* lam, const float* mu, const float* rho,
+                      const float* resid, const float* in, float* out, const float* hist_hi,
+                      float* acc, float* acc_rho, float* acc_h, int xm)
+{
+    const int tz = 64 - 2 * T;
+#define BHFWI_MA(TT, XX)                                                                      \
+    hipLaunchKernelGGL((bhfwi::march::k_adj_march<TT, XX>), dim3(na), dim3(64), 0, st,        \
+                       c->d_shots, ts.d[0], na, c->tune.tile_map, tz, n_hi, lam, mu, rho,     \
+                       c->d_rec, resid, c->d_pml_r, in, out, hist_hi,                         \
+                       (long long)(2 * c->cells), acc, acc_rho, acc_h, c->wgrad,              \
+                       (long long)c->cells)
+#define BHFWI_ML(TT)                         \
+    case TT:                                 \
+        switch (xm) {                        \
+        case 1: BHFWI_MA(TT, 1); break;      \
+        case 2: BHFWI_MA(TT, 2); break;      \
+        case 3: BHFWI_MA(TT, 3); break;      \
+        case 4: BHFWI_MA(TT, 4); break;      \
+        default: BHFWI_MA(TT, 0); break;     \
+        }                                    \
+        break;
+    switch (nsteps) { BHFWI_MARCH(BHFWI_ML) }
+#undef BHFWI_ML
+#undef BHFWI_MA
+}
+
 #define BHFWI_TB(TT, RR, WW)                                                                 \
     if (T == TT && TRE == RR && W == WW) {                                                   \
         hipLaunchKernelGGL((bhfwi::k_fwd_tb<TT, RR, WW, PMV>), dim3(nact), dim3(64 * WW), 0, \
@@ -797,14 +949,20 @@ void fwd_tb_launch(bhfwi_ctx* c, hipStream_t st, int n0, int nsteps, const float
                    const float* mu, const float* rho, const float* wav, const float* in,
                    float* out, float* traces, float* hist)
 {
-    const TileSet& ts = c->ftiles;
+    const bool march = !c->fmarch.t[1].empty();
+    const TileSet& ts = march ? c->fmarch : c->ftiles;
     const int na[2] = {active_tiles(ts, 0, n0), active_tiles(ts, 1, n0)};
     if (na[0] + na[1] <= 0) return;
     EvScope ev(c, st, hist ? 1 : 0);
-    PmlFork fork(c, st, na);
+    PmlFork fork(c, st, na, march);
     for (int q = 0; q < 2; ++q) {
         const int nact = na[q];
         if (nact <= 0) continue;
+        if (march && q == 0) {
+            fwd_march_launch(c, fork.stream(q), ts, nact, n0, nsteps, lam, mu, rho, wav, in, out,
+                             traces, hist);
+            continue;
+        }
         const Shape sh = q ? ts.pml : fwd_shape(c);
         const int T = sh.T, TRE = sh.TRE, W = sh.W;
         if (q == 0) {
@@ -855,15 +1013,21 @@ void adj_tb_launch(bhfwi_ctx* c, hipStream_t st, int n_hi, int nsteps, const flo
     const Shape xs = adj_x_shape(c);
     // the extra register sums need the alternative shape; the wavelet record does not
     const bool alt = (xm & 3) != 0 && xs.T >= 2;
-    const TileSet& ts = alt ? c->xtiles : c->atiles;
+    const bool march = !c->amarch.t[1].empty();
+    const TileSet& ts = march ? c->amarch : alt ? c->xtiles : c->atiles;
     const int n_lo = n_hi - nsteps + 1;
     const int na[2] = {active_tiles(ts, 0, n_lo), active_tiles(ts, 1, n_lo)};
     if (na[0] + na[1] <= 0) return;
     EvScope ev(c, st, 2);
-    PmlFork fork(c, st, na);
+    PmlFork fork(c, st, na, march);
     for (int q = 0; q < 2; ++q) {
         const int nact = na[q];
         if (nact <= 0) continue;
+        if (march && q == 0) {
+            adj_march_launch(c, fork.stream(q), ts, nact, adj_shape(c).T, n_hi, nsteps, lam, mu,
+                             rho, resid, in, out, hist_hi, acc, acc_rho, acc_h, xm);
+            continue;
+        }
         const Shape sh = q ? ts.pml : alt ? xs : adj_shape(c);
         const int T = sh.T, TRE = sh.TRE, W = sh.W;
         if (q == 0) {
@@ -1116,13 +1280,13 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
         wv += h.nt;
         S.pml_r_off = pr_off;
         S.pml_z_off = pz_off;
-        pr_off += 4 * (int)NR;
+        pr_off += 6 * (int)NR;
         pz_off += 4 * (int)NZ;
         // PML tables: [a_int | b_int | a_half | b_half]
         const double lnR = std::log(1e-4);
         const double d0r = h.npml_r > 0 ? -3.0 * h.pml_vmax * lnR / (2.0 * h.npml_r * h.dr) : 0.0;
         const double d0z = h.npml_z > 0 ? -3.0 * h.pml_vmax * lnR / (2.0 * h.npml_z * h.dz) : 0.0;
-        std::vector<float> tr_(4 * NR), tz_(4 * NZ);
+        std::vector<float> tr_(6 * NR), tz_(4 * NZ);
         for (int i = 0; i < NR; ++i) {
             double xi = 0, xh = 0;
             if (h.npml_r > 0) {
@@ -1143,6 +1307,7 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
             pml_coef(xi, d0z, h.f0, h.dt, &tz_[k], &tz_[NZ + k]);
             pml_coef(xh, d0z, h.f0, h.dt, &tz_[2 * NZ + k], &tz_[3 * NZ + k]);
         }
+        // [4 NR, 6 NR): the 1/(2 r) factors, filled on the device (k_radii)
         pmr.insert(pmr.end(), tr_.begin(), tr_.end());
         pmz.insert(pmz.end(), tz_.begin(), tz_.end());
         c->sd.push_back(S);
@@ -1180,6 +1345,9 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
         CREATE_HIP(hipMemcpy(c->d_rec, rec_k, sizeof(int) * nrec_total, hipMemcpyHostToDevice));
     CREATE_HIP(hipMalloc(&c->d_pml_r, sizeof(float) * pmr.size()));
     CREATE_HIP(hipMemcpy(c->d_pml_r, pmr.data(), sizeof(float) * pmr.size(), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(bhfwi::march::k_radii, dim3((unsigned)nshot), dim3(256), 0, nullptr,
+                       c->d_shots, c->d_pml_r);
+    CREATE_HIP(hipGetLastError());
     CREATE_HIP(hipMalloc(&c->d_pml_z, sizeof(float) * pmz.size()));
     CREATE_HIP(hipMemcpy(c->d_pml_z, pmz.data(), sizeof(float) * pmz.size(), hipMemcpyHostToDevice));
     CREATE_HIP(hipMalloc(&c->d_scratch, 4 * sizeof(float) * kPartBlocks + sizeof(double) * kPartBlocks));
@@ -1187,6 +1355,9 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
     CREATE_HIP(hipMemset(c->d_status, 0, sizeof(int)));
 #undef CREATE_HIP
     if (int rc = upload_work(c)) return bail(rc);
+    if (hipStreamSynchronize(nullptr) != hipSuccess)  // the radius tables, for every stream
+        return bail(fail(c, BHFWI_EHIP, "bhfwi_create: synchronise"));
+    *out = c;
     return BHFWI_OK;
 }
 
@@ -1217,6 +1388,8 @@ void bhfwi_destroy(bhfwi_ctx* c)
         if (c->atiles.d[q]) (void)hipFree(c->atiles.d[q]);
         if (c->xtiles.d[q]) (void)hipFree(c->xtiles.d[q]);
         if (c->f4tiles.d[q]) (void)hipFree(c->f4tiles.d[q]);
+        if (c->fmarch.d[q]) (void)hipFree(c->fmarch.d[q]);
+        if (c->amarch.d[q]) (void)hipFree(c->amarch.d[q]);
     }
     if (c->d_scratch) (void)hipFree(c->d_scratch);
     if (c->d_status) (void)hipFree(c->d_status);
