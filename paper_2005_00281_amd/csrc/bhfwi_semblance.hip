@@ -11,6 +11,15 @@
 // workgroup scan), and then takes every window's sums as a difference of two
 // prefix values.  The time range of a chunk is at most kSemSpan samples, so
 // the LDS footprint does not depend on the record length.
+//
+// The interpolated reads bound it (13 receivers per staged sample).  A thread
+// holds its eight samples' stacks in registers with the receivers as the outer
+// loop, so a receiver's shift is uniform (scalar registers) and, where the
+// whole span of a receiver lies inside the record, a read is one unconditional
+// 8-byte load (the two neighbours of the interpolation) and four vector
+// operations; chunks at the ends of the record take the tests per sample.  The
+// prefix arrays are padded by one double in nine, because the scan reads eight
+// consecutive doubles per lane.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -24,92 +33,138 @@ constexpr int kSemSpan = 2048;  // samples staged per workgroup
 constexpr int kSemThreads = 256;
 constexpr int kSemPer = kSemSpan / kSemThreads;  // samples per thread in the scan
 
-__global__ void __launch_bounds__(kSemThreads)
+// Place of prefix entry k: one double of padding after every kSemPer, so that
+// lanes that read kSemPer consecutive entries each spread over the LDS banks.
+__device__ __forceinline__ int sem_at(int k) { return k + k / kSemPer; }
+
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ double sem_wave_scan(double v, int lane)
+{
+    for (int o = 1; o < 64; o <<= 1) {
+        const double u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+    }
+    return v;
+}
+
+__global__ void __launch_bounds__(kSemThreads, 4)
 k_semblance(int nrec, int nt, const float* __restrict__ traces, float dt,
             const float* __restrict__ offset, float p0, float dp, int ntau, int stride, int win,
             int chunk, float* __restrict__ coh, float* __restrict__ energy)
 {
     // Ps[k], Pe[k]: first the squared stack and the energy of sample
     // n_lo + k - 1, then (in place) their prefix sums over samples < n_lo + k
-    __shared__ double Ps[kSemSpan + 1];
-    __shared__ double Pe[kSemSpan + 1];
-    __shared__ double Ts[kSemThreads], Te[kSemThreads];  // per-thread totals, scanned
+    __shared__ double Ps[kSemSpan + kSemSpan / kSemPer + 1];
+    __shared__ double Pe[kSemSpan + kSemSpan / kSemPer + 1];
+    __shared__ double Tw[2][kSemThreads / 64];  // totals of each wave
     __shared__ int Lq[64];                 // per receiver: whole samples of the shift
     __shared__ float Lf[64];               // and its fraction
     const int j = blockIdx.x, g = blockIdx.y;
     const int i0 = blockIdx.z * chunk;
     const int i1 = min(ntau, i0 + chunk);
     if (i0 >= i1) return;  // uniform
-    const int np = gridDim.x;
+    const int np = gridDim.x, tid = threadIdx.x;
     const float* __restrict__ x = traces + (long long)g * nrec * nt;
-    if ((int)threadIdx.x < nrec) {
+    if (tid < nrec) {
         // the shift p offset / dt in double, once per receiver, split into
         // whole samples and a fraction (large shifts keep their fraction)
         const double s = ((double)p0 + j * (double)dp) *
-                         (double)offset[(long long)g * nrec + threadIdx.x] / (double)dt;
+                         (double)offset[(long long)g * nrec + tid] / (double)dt;
         const double fl = floor(s);
-        Lq[threadIdx.x] = (int)fl;
-        Lf[threadIdx.x] = (float)(s - fl);
+        Lq[tid] = (int)fl;
+        Lf[tid] = (float)(s - fl);
     }
     __syncthreads();
     const int n_lo = i0 * stride;
     const int n_hi = min((i1 - 1) * stride + win, n_lo + kSemSpan);
     const int len = n_hi - n_lo;
-    for (int n = n_lo + (int)threadIdx.x; n < n_hi; n += kSemThreads) {
-        float st = 0.f, en = 0.f;
-        for (int m = 0; m < nrec; ++m) {
-            const int q = n + Lq[m];  // sample at or before the shifted time
-            const float f = Lf[m];
-            const float* __restrict__ xm = x + (long long)m * nt;
-            const float a = (q >= 0 && q < nt) ? xm[q] : 0.f;
-            const float b = (q + 1 >= 0 && q + 1 < nt) ? xm[q + 1] : 0.f;
-            // the shifted time lies inside the record, or at its last sample
-            float v = 0.f;
-            if (q >= 0 && (q < nt - 1 || (q == nt - 1 && f == 0.f))) v = a + f * (b - a);
-            st += v;
-            en += v * v;
+    float st[kSemPer], en[kSemPer];  // samples n_lo + tid + r kSemThreads
+#pragma unroll
+    for (int r = 0; r < kSemPer; ++r) st[r] = en[r] = 0.f;
+    for (int m = 0; m < nrec; ++m) {
+        const int q0 = __builtin_amdgcn_readfirstlane(Lq[m]);
+        const float f = __builtin_bit_cast(
+            float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, Lf[m])));
+        const float* __restrict__ xm = x + (long long)m * nt;
+        const long long first = (long long)n_lo + q0;  // sample read for n_lo
+        if (first >= 0 && first + kSemSpan < nt) {  // uniform: every read inside the record
+            const float* __restrict__ xr = xm + first;
+            float a[kSemPer], b[kSemPer];
+#pragma unroll
+            for (int r = 0; r < kSemPer; ++r) {
+                a[r] = xr[tid + r * kSemThreads];
+                b[r] = xr[tid + r * kSemThreads + 1];
+            }
+#pragma unroll
+            for (int r = 0; r < kSemPer; ++r) {
+                const float v = a[r] + f * (b[r] - a[r]);
+                st[r] += v;
+                en[r] += v * v;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < kSemPer; ++r) {
+                // sample at or before the shifted time
+                const long long q = first + tid + r * kSemThreads;
+                const float a = (q >= 0 && q < nt) ? xm[q] : 0.f;
+                const float b = (q + 1 >= 0 && q + 1 < nt) ? xm[q + 1] : 0.f;
+                // the shifted time lies inside the record, or at its last sample
+                float v = 0.f;
+                if (q >= 0 && (q < nt - 1 || (q == nt - 1 && f == 0.f))) v = a + f * (b - a);
+                st[r] += v;
+                en[r] += v * v;
+            }
         }
-        Ps[n - n_lo + 1] = (double)st * st;
-        Pe[n - n_lo + 1] = en;
+    }
+#pragma unroll
+    for (int r = 0; r < kSemPer; ++r) {
+        const int k = tid + r * kSemThreads + 1;
+        if (k <= len) {
+            Ps[sem_at(k)] = (double)st[r] * st[r];
+            Pe[sem_at(k)] = en[r];
+        }
     }
     __syncthreads();
     // prefix sums in double: each thread totals kSemPer consecutive samples,
-    // the totals are scanned (Hillis-Steele), then each thread turns its own
+    // the totals are scanned over the workgroup, then each thread turns its own
     // samples into running sums
-    const int t0 = threadIdx.x * kSemPer + 1;
-    double ts = 0.0, te = 0.0;
-    for (int q = 0; q < kSemPer; ++q)
-        if (t0 + q <= len) {
-            ts += Ps[t0 + q];
-            te += Pe[t0 + q];
-        }
-    Ts[threadIdx.x] = ts;
-    Te[threadIdx.x] = te;
-    __syncthreads();
-    for (int o = 1; o < kSemThreads; o <<= 1) {
-        const double as = threadIdx.x >= (unsigned)o ? Ts[threadIdx.x - o] : 0.0;
-        const double ae = threadIdx.x >= (unsigned)o ? Te[threadIdx.x - o] : 0.0;
-        __syncthreads();
-        Ts[threadIdx.x] += as;
-        Te[threadIdx.x] += ae;
-        __syncthreads();
+    const int t0 = tid * kSemPer + 1, lane = tid & 63, wave = tid >> 6;
+    double vs[kSemPer], ve[kSemPer], ts = 0.0, te = 0.0;
+#pragma unroll
+    for (int q = 0; q < kSemPer; ++q) {
+        const bool ok = t0 + q <= len;
+        vs[q] = ok ? Ps[sem_at(t0 + q)] : 0.0;
+        ve[q] = ok ? Pe[sem_at(t0 + q)] : 0.0;
+        ts += vs[q];
+        te += ve[q];
     }
-    double rs = Ts[threadIdx.x] - ts, re = Te[threadIdx.x] - te;  // exclusive
+    const double ss = sem_wave_scan(ts, lane), se = sem_wave_scan(te, lane);
+    if (lane == 63) {
+        Tw[0][wave] = ss;
+        Tw[1][wave] = se;
+    }
+    __syncthreads();
+    double rs = ss - ts, re = se - te;  // exclusive
+    for (int w = 0; w < wave; ++w) {
+        rs += Tw[0][w];
+        re += Tw[1][w];
+    }
+#pragma unroll
     for (int q = 0; q < kSemPer; ++q)
         if (t0 + q <= len) {
-            rs += Ps[t0 + q];
-            re += Pe[t0 + q];
-            Ps[t0 + q] = rs;
-            Pe[t0 + q] = re;
+            rs += vs[q];
+            re += ve[q];
+            Ps[sem_at(t0 + q)] = rs;
+            Pe[sem_at(t0 + q)] = re;
         }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         Ps[0] = 0.0;
         Pe[0] = 0.0;
     }
     __syncthreads();
-    for (int i = i0 + (int)threadIdx.x; i < i1; i += kSemThreads) {
-        const int a0 = i * stride - n_lo;
-        const double num = Ps[a0 + win] - Ps[a0], den = Pe[a0 + win] - Pe[a0];
+    for (int i = i0 + tid; i < i1; i += kSemThreads) {
+        const int a0 = sem_at(i * stride - n_lo), a1 = sem_at(i * stride - n_lo + win);
+        const double num = Ps[a1] - Ps[a0], den = Pe[a1] - Pe[a0];
         const long long o = ((long long)g * np + j) * ntau + i;
         coh[o] = den > 0.0 ? (float)(num / (nrec * den)) : 0.f;
         if (energy) energy[o] = (float)den;
