@@ -57,6 +57,7 @@ k_adj_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
     const int k = wk.y - T + lane;  // interior tiles: the owned lanes and their halo lie in the grid
     const bool own = lane >= T && lane < T + tz;
     const unsigned kb = 4u * (unsigned)min(k, NZ - 1);
+    const unsigned kmb = 4u * (unsigned)min(k + (lane == 63), NZ - 1);
     // the correlation of the owned cells reads one column around them only
     const unsigned khb = 4u * (unsigned)min(max(k, wk.y - 1), wk.y + tz);
     const float dt = S.dt, idr = S.inv_dr, idz = S.inv_dz;
@@ -113,7 +114,7 @@ k_adj_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
     const int sbeg = max(0, i0 - T), send = i1 - 1 + T;
     long long hstr = hist_stride;
     Row P{};
-    float p_lam, p_mu, p_rho, mu_prev = 0.f, rho_prev = 1.f, bZ_prev = 0.f;
+    float p_lam, p_mu, p_muk, p_rho, mu_prev = 0.f, muk_prev = 0.f, rho_prev = 1.f, bZ_prev = 0.f;
     auto fetch = [&](int i) {  // adjoint state and model of row i (inside the grid: i <= send + 1)
         const unsigned c = kb + (unsigned)(i * rowB), m = kb + (unsigned)(i * rowM);
         p_rR = rRt[i];
@@ -126,6 +127,7 @@ k_adj_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
         P.trz = ldrow(Ai + 5 * cells, c);
         p_lam = ldrow(lam_m, m);
         p_mu = ldrow(mu_m, m);
+        p_muk = ldrow(mu_m, kmb + (unsigned)(i * rowM));
         p_rho = ldrow(rho_m, m);
     };
     // stored velocities that level t takes in march step s: v_r of row s - t and
@@ -142,6 +144,7 @@ k_adj_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
     };
     if (sbeg >= 1) {
         mu_prev = ldrow(mu_m, kb + (unsigned)((sbeg - 1) * rowM));
+        muk_prev = ldrow(mu_m, kmb + (unsigned)((sbeg - 1) * rowM));
         rho_prev = ldrow(rho_m, kb + (unsigned)((sbeg - 1) * rowM));
     }
     fetch(sbeg);
@@ -155,7 +158,14 @@ k_adj_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
         if constexpr (GEN) {
             if (s == 0) in.vr = in.trz = 0.f;  // nodes on the axis
         }
-        const Coef cf = coefs(dt, p_lam, p_mu, p_rho, mu_prev, rho_prev, !GEN || s >= 1);
+        // the last lane's driver reaches the lane below it in the same step: it takes
+        // the column above it from memory (after the exchange: all lanes take part)
+        float mu_kp = from_lane_above(p_mu), mu_mkp = from_lane_above(mu_prev);
+        mu_kp = lane == 63 ? p_muk : mu_kp;
+        mu_mkp = lane == 63 ? muk_prev : mu_mkp;
+        const Coef cf = coefs(dt, p_lam, p_mu, p_rho, mu_prev, rho_prev, mu_kp, mu_mkp,
+                              !GEN || s >= 1);
+        muk_prev = p_muk;
         mu_prev = p_mu;
         rho_prev = p_rho;
 #pragma unroll

@@ -65,19 +65,20 @@ __device__ inline float* scalar_row(float* p)
 
 // Medium coefficients of one row, from the model values of the row and the
 // row below it; up: the row has one below it (v_r and tau_rz vanish on the
-// axis).  The last lane has no neighbour above it: its values are halo.
+// axis).  mu_kp and mu_mkp: the rigidities of the column above.  The last
+// lane's bZ lacks its neighbour: only its own v_z takes it, which is halo.
 struct Coef {
     float cl, c2m, bR, bZ, mS;
 };
 __device__ inline Coef coefs(float dt, float lam, float mu, float rho, float mu_m, float rho_m,
-                             bool up)
+                             float mu_kp, float mu_mkp, bool up)
 {
     Coef c;
     c.cl = dt * lam;
     c.c2m = dt * 2.0f * mu;
     c.bR = up ? dt * 2.0f * rcp(rho_m + rho) : 0.f;
     c.bZ = dt * 2.0f * rcp(rho + from_lane_above(rho));
-    c.mS = up ? dt * mu_harm(mu_m, mu, from_lane_above(mu_m), from_lane_above(mu)) : 0.f;
+    c.mS = up ? dt * mu_harm(mu_m, mu, mu_mkp, mu_kp) : 0.f;
     return c;
 }
 
@@ -200,7 +201,10 @@ k_fwd_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
     auto step = [&](int s, auto GENC) {
         constexpr bool GEN = decltype(GENC)::value != 0;
         Row in = P;
-        const Coef cf = coefs(dt, p_lam, p_mu, p_rho, mu_prev, rho_prev, !GEN || s >= 1);
+        // the last lane's tau_rz is halo from the first step on: its rigidity may
+        // lack the neighbour
+        const Coef cf = coefs(dt, p_lam, p_mu, p_rho, mu_prev, rho_prev, from_lane_above(p_mu),
+                              from_lane_above(mu_prev), !GEN || s >= 1);
         mu_prev = p_mu;
         rho_prev = p_rho;
         L[(s - 1) & (kRing - 1)][4][lane] = cf.bR;  // read with row s - 1

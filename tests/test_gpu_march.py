@@ -116,3 +116,35 @@ def test_marches_match_the_oracle(tb, atb, nt, K, extra):
                     r[off: off + nrec * n])
                 assert abs(lhs - rhs) <= 1e-5 * scale
             o += sh.nt
+
+
+@pytest.mark.parametrize("T", [4, 6])
+def test_last_owned_lane(T):
+    """Column by column, the march's correlations against those of the same shot
+    alone, which the LDS tiles run: the lane beside a strip's last sound one must
+    not reach it within a block.  Bar: the two differ by the rounding of some 300
+    steps, about 6e-8 * sqrt(4 * 300) = 2e-6, times 5 for one column's norm."""
+    import paper_2005_00281_amd as P
+    print("[case] march strips", T, flush=True)
+    w = _batch(300, 150, 288, 6, 301)
+    rng = np.random.default_rng(6)
+    rho = _f32(w.rho)
+    lam, mu = P.moduli(_f32(w.vp_start), _f32(w.vs_start), rho)
+    acc, s = [], 149
+    for shots in (w.shots, w.shots[s:s + 1]):
+        sv = P.Survey(shots, (w.NRg, w.NZg), ckpt_every=50)
+        sv.set_tune(tb_steps=8, tb_rows=48, tb_waves=16, adj_tb_steps=T, adj_tb_rows=32,
+                    adj_tb_waves=16)
+        sv.fwd_model(lam, mu, rho, sv.pack_wavelets([x.wavelet for x in shots]),
+                     store_ckpt=True)
+        r = np.zeros(sv.sizes.trace_elems, np.float32)
+        j = len(acc) == 0 and s or 0
+        off, nrec, n = sv.trace_slices()[j]
+        if not acc:
+            res = rng.standard_normal(nrec * n).astype(np.float32)
+        r[off: off + nrec * n] = res
+        a = sv.adjoint_model(lam, mu, rho, sv.pack_wavelets([x.wavelet for x in shots]), _f32(r))
+        acc.append([v.cpu().numpy().astype(np.float64) for v in sv.acc_views(a)[j]])
+    for q, (a, b) in enumerate(zip(*acc)):
+        e, n = np.linalg.norm(a - b, axis=0), np.linalg.norm(b, axis=0)
+        assert (e <= 1e-5 * np.maximum(n, n.mean())).all(), (q, (e / np.maximum(n, n.mean())).max())
