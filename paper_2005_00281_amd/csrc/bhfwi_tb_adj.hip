@@ -205,21 +205,24 @@ k_adj_tb(const ShotDev* __restrict__ shots, const int4* __restrict__ work, int n
         b_rh[j] = wave_uniform(b_rh[j]);
     }
 
-    // the residual of every step of this launch at this lane's receiver (if
-    // the lane's axial row holds one), staged once
+    // the residual of every step of this launch at the receiver of each lane's
+    // axial row (at most one per row), staged once where the window holds the
+    // axis row: a lane per receiver, not a chain of nrec loads in every tile
     if (wave == 0) {
-        float rsum[T];
 #pragma unroll
-        for (int t = 0; t < T; ++t) rsum[t] = 0.f;
-        for (int r = 0; r < S.nrec; ++r)
-            if (kin && rec_k[S.rec_off + r] == k) {
+        for (int t = 0; t < T; ++t) Lres[t][lane] = 0.f;
+        if (wk.z - T <= 0)
+            for (int r0 = 0; r0 < S.nrec; r0 += 64) {
+                const int r = r0 + lane;
+                const int col = r < S.nrec ? rec_k[S.rec_off + r] - (wk.y - T) : -1;
+                if (col >= 0 && col < 64) {
+                    const float* __restrict__ rs =
+                        resid + S.trace_off + (long long)r * S.nt + n_hi;
 #pragma unroll
-                for (int t = 0; t < T; ++t)
-                    if (t >= t0 && t < nsteps)
-                        rsum[t] += resid[S.trace_off + (long long)r * S.nt + (n_hi - t)];
+                    for (int t = 0; t < T; ++t)
+                        if (t >= t0 && t < nsteps) Lres[t][col] = rs[-t] * (1.0f / 3.0f);
+                }
             }
-#pragma unroll
-        for (int t = 0; t < T; ++t) Lres[t][lane] = rsum[t] * (1.0f / 3.0f);
     }
     // stored v^{n+1/2} of the first step; later steps are fetched one step ahead.
     // The correlation of the owned cells reads it on the owned tile and one

@@ -32,6 +32,18 @@ struct IntC {
     static constexpr int value = V;
 };
 
+// For the 64 axial rows from k0 on: the receiver (at most one per row) of each,
+// or -1.  One wave, a lane per receiver: one load in place of a chain of nrec.
+__device__ inline void stage_receivers(int* Lrec, const int* __restrict__ rec_k, int nrec, int k0,
+                                       int lane)
+{
+    Lrec[lane] = -1;
+    for (int r0 = 0; r0 < nrec; r0 += 64) {
+        const int c = r0 + lane < nrec ? rec_k[r0 + lane] - k0 : -1;
+        if (c >= 0 && c < 64) Lrec[c] = r0 + lane;
+    }
+}
+
 template <int T, int TRE, int W, int PM>
 __global__ void __launch_bounds__(64 * W, (W >= 16 && (TRE == W || (PM == 0 && TRE <= 3 * W))) ? 8 : 1)
 k_fwd_tb(const ShotDev* __restrict__ shots, const int4* __restrict__ work, int nwork, int map,
@@ -49,6 +61,7 @@ k_fwd_tb(const ShotDev* __restrict__ shots, const int4* __restrict__ work, int n
     enum { TRR = 0, TTT, TRZ, VR, VZ, NPL };
     __shared__ float L[NPL][LDW];
     __shared__ float Lwav[T];  // source samples of this launch's steps
+    __shared__ int Lrec[64];   // receiver recorded by each lane's axial row, or -1
 
     const int wg = xcd_chunk(blockIdx.x, nwork, map);
     if (wg >= nwork) return;
@@ -90,12 +103,8 @@ k_fwd_tb(const ShotDev* __restrict__ shots, const int4* __restrict__ work, int n
             L[f][(TRE + 1) * 64 + lane] = 0.f;
         }
         if (lane < T) Lwav[lane] = lane < ns ? wavelet[S.wave_off + n0 + lane] : 0.f;
+        if (traces && wk.z == 0) stage_receivers(Lrec, rec_k + S.rec_off, S.nrec, wk.y - T, lane);
     }
-    // receiver recorded by this lane's axial row (first match), or -1
-    int rj = -1;
-    if (traces && wk.z == 0)
-        for (int r = S.nrec - 1; r >= 0; --r)
-            if (kin && rec_k[S.rec_off + r] == k) rj = r;
 
     // per cell (registers) and per row (wave-uniform) state
     float vr[RPT], vz[RPT], trr[RPT], ttt[RPT], tzz[RPT], trz[RPT];
@@ -179,6 +188,7 @@ k_fwd_tb(const ShotDev* __restrict__ shots, const int4* __restrict__ work, int n
         L[VZ][x] = vz[j];
     }
     __syncthreads();
+    const int rj = traces && wk.z == 0 ? Lrec[lane] : -1;
 
     // byte offset of this lane's cell in each row within a history plane
     unsigned hoff[RPT];
