@@ -62,7 +62,9 @@ ADJ_BLOCK_BYTES_PER_CELL_X = 16
 # sources it was measured on (SHA-256 of PMC_SOURCES: the adjoint block kernel
 # and the device code it includes), the same shapes, tile map and workload;
 # otherwise traffic is null.
-PMC_SOURCES = ("paper_2005_00281_amd/csrc/bhfwi_tb_adj.hip",
+PMC_SOURCES = ("paper_2005_00281_amd/csrc/bhfwi_march_adj.hip",
+               "paper_2005_00281_amd/csrc/bhfwi_march_fwd.hip",
+               "paper_2005_00281_amd/csrc/bhfwi_tb_adj.hip",
                "paper_2005_00281_amd/csrc/bhfwi_tb_fwd.hip",
                "paper_2005_00281_amd/csrc/bhfwi_kernels.hip",
                "paper_2005_00281_amd/csrc/bhfwi_internal.h")
@@ -308,7 +310,8 @@ def trace_gaps(path):
         for r in csv.DictReader(f):
             ev.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), r["Kernel_Name"]))
     ev.sort()
-    step = ("k_fwd_tb", "k_adj_tb", "k_fwd_step", "k_adj_step", "k_fwd4", "k_adj4")
+    step = ("k_fwd_march", "k_adj_march", "k_fwd_tb", "k_adj_tb", "k_fwd_step", "k_adj_step",
+            "k_fwd4", "k_adj4")
     is_step = [any(x in name for x in step) for _, _, name in ev]
     busy, end_max, gaps, step_gaps = 0, None, [], []
     for j, (t0, t1, _) in enumerate(ev):
@@ -692,8 +695,9 @@ def kernel_roofline(args, inv, surveys, tune, full):
          b4[0] if (args.order == 4 and b4[0] >= 2) else 1)
     kname = (("k_adj4_tb<%d, %d, %d, 0, %d> + k_adj4_tb<%d, %d, %d, 1, %d>" % (
               b4 + (xm,) + b4 + (xm,)) if b4[0] >= 2 else "k_adj4<%d>" % xm) if args.order == 4
-             else "k_adj_tb<%d, %d, %d, 0, %d> + k_adj_tb<%d, %d, %d, 1, %d>" % (
-             ka + (xm,) + kp + (xm,))
+             else "k_adj_march<%d, %d> (k_adj_tb<%d, %d, %d, 0, %d> where the survey is too "
+                  "small for the marches) + k_adj_tb<%d, %d, %d, 1, %d>" % (
+             (ka[0], xm) + ka + (xm,) + kp + (xm,))
              if ka[0] >= 2
              else "k_adj_step<%d>" % (tune["rows_per_wave"] if tune["rows_per_wave"] <= 4 else 0))
     adj_avg_s = adj_ms * 1e-3 / adj_n

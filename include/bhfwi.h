@@ -262,11 +262,11 @@ int bhfwi_plan(const bhfwi_shot *shots, int32_t nshot, int64_t budget_bytes,
                bhfwi_plan_info *info);
 
 /* The temporally blocked kernel shapes the current tune runs, 18 int32 to
- * out (host; surveys with enough columns to fill the GPU run their tiles clear
- * of the PML as register marches of the same T instead, and surveys whose
- * tiles fit the GPU in one round run them all in the PML kernel): (T, rows, waves) of the forward kernel on tiles clear of the
+ * out (host): (T, rows, waves) of the forward kernel on tiles clear of the
  * PML, of the forward kernel on the PML sub-tiles, the same two for the
- * adjoint, and the same two for the adjoint with extra outputs
+ * adjoint (surveys with enough columns to fill the GPU run their tiles clear
+ * of the PML as register marches of the same T instead, and surveys whose
+ * tiles fit the GPU in one round run them all in the PML kernel), and the same two for the adjoint with extra outputs
  * (bhfwi_adjoint_model_ex): an interior adjoint shape with four rows per
  * thread runs those as the shape with three rows per thread, same T and
  * waves (8x64x16 -> 8x48x16), whose registers hold the extra sums; T = 0

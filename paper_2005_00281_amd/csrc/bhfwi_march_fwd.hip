@@ -23,6 +23,10 @@
 // PML layer stay with the LDS tiles: the memories would double the registers a
 // level keeps.
 //
+// What bounds it: vector issue and memory together (the recompute march moves
+// 3.76 TB/s of HBM traffic where a copy moves 5.0).  12 shots of 276 x 4136
+// cells, 1250 steps: 52.0 ms, 72.9 in LDS tiles.
+//
 // The product-sums are explicit (contraction off) and fused where the compiler
 // fuses them in the LDS tiles, so a cell's value does not depend on which of the
 // two, or which tile, computed it.
