@@ -264,14 +264,24 @@ int bhfwi_plan(const bhfwi_shot *shots, int32_t nshot, int64_t budget_bytes,
 /* The temporally blocked kernel shapes the current tune runs, 18 int32 to
  * out (host): (T, rows, waves) of the forward kernel on tiles clear of the
  * PML, of the forward kernel on the PML sub-tiles, the same two for the
- * adjoint (surveys with enough columns to fill the GPU run their tiles clear
- * of the PML as register marches of the same T instead, and surveys whose
- * tiles fit the GPU in one round run them all in the PML kernel), and the same two for the adjoint with extra outputs
+ * adjoint, and the same two for the adjoint with extra outputs
  * (bhfwi_adjoint_model_ex): an interior adjoint shape with four rows per
  * thread runs those as the shape with three rows per thread, same T and
  * waves (8x64x16 -> 8x48x16), whose registers hold the extra sums; T = 0
- * where that part runs one step per launch. */
+ * where that part runs one step per launch.  Surveys with enough columns to
+ * fill the GPU run their tiles clear of the PML as register marches of the
+ * same T instead, and surveys whose tiles fit the GPU in one round run them
+ * all in the PML kernel: bhfwi_kernel_tiles says which. */
 int bhfwi_kernel_shapes(const bhfwi_ctx *ctx, int32_t *out);
+
+/* The tiles those kernels run on (second order), 9 int32 to out (host): for
+ * the forward, the adjoint and the adjoint with extra outputs each
+ * (m, clear, pml).  m > 0: the tiles clear of the PML are register marches of
+ * at most m radial rows; m = 0: they are LDS tiles.  clear: number of those
+ * tiles; pml: number of tiles the kernel with the PML memories runs (all of
+ * them where one launch runs a whole block).  0, 0, 0 where that part runs one
+ * step per launch. */
+int bhfwi_kernel_tiles(const bhfwi_ctx *ctx, int32_t *out);
 
 /* Read (and with reset != 0 clear) the sums of bhfwi_kernel_times_t. */
 int bhfwi_kernel_times(bhfwi_ctx *ctx, bhfwi_kernel_times_t *out, int32_t reset);

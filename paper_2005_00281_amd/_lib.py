@@ -85,7 +85,7 @@ EXPORTS = ["bhfwi_build_id", "bhfwi_create", "bhfwi_destroy", "bhfwi_last_error"
            "bhfwi_adjoint_model_ex", "bhfwi_gradient_hessian", "bhfwi_precondition_diag",
            "bhfwi_radial_taper", "bhfwi_update_density", "bhfwi_set_order",
            "bhfwi_set_order4_blocks",
-           "bhfwi_misfit_noalloc", "bhfwi_adjoint_model_wavelet"]
+           "bhfwi_misfit_noalloc", "bhfwi_adjoint_model_wavelet", "bhfwi_kernel_tiles"]
 
 _lib = None
 
@@ -145,6 +145,7 @@ def load(path: str = LIB_PATH):
     L.bhfwi_line_search.argtypes = [P, V, P, P, P, P, P]
     L.bhfwi_status.argtypes = [P, V]
     L.bhfwi_kernel_shapes.argtypes = [P, C.POINTER(C.c_int32)]
+    L.bhfwi_kernel_tiles.argtypes = [P, C.POINTER(C.c_int32)]
     L.bhfwi_semblance.argtypes = [V, I32, I32, I32, P, F, P, I32, F, F, I32, I32, I32, P, P]
     L.bhfwi_semblance_pick.argtypes = [V, I32, I32, I32, P, P, F, F, F, P, F, F, F, P, P, P]
     L.bhfwi_starting_model.argtypes = [V, I32, I32, F, F, F, P, P, P, P, F, P, P]
@@ -438,6 +439,14 @@ class Survey:
         _check(load().bhfwi_kernel_shapes(self._h, out), self._h)
         names = ("fwd", "fwd_pml", "adj", "adj_pml", "adj_x", "adj_x_pml")
         return {n: tuple(out[3 * q: 3 * q + 3]) for q, n in enumerate(names)}
+
+    def kernel_tiles(self):
+        """{'fwd', 'adj', 'adj_x'}: (rows of a march tile or 0 for LDS tiles,
+        tiles clear of the PML, tiles of the PML kernel) of the temporally
+        blocked launches (bhfwi_kernel_tiles)."""
+        out = (C.c_int32 * 9)()
+        _check(load().bhfwi_kernel_tiles(self._h, out), self._h)
+        return {n: tuple(out[3 * q: 3 * q + 3]) for q, n in enumerate(("fwd", "adj", "adj_x"))}
 
     def get_tune(self):
         t = Tune()

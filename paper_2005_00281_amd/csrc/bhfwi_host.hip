@@ -150,6 +150,7 @@ struct TileSet {
     std::vector<int> nt[2];
     int4* d[2] = {nullptr, nullptr};
     Shape pml{0, 0, 0};
+    int rows = 0;  // marches: most radial rows of a tile of list 0
 };
 
 struct bhfwi_ctx {
@@ -431,6 +432,7 @@ void build_march(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Sh
     }
     ts->pml = pml;
     const int T = sh.T, R = march_rows(c, T);
+    ts->rows = R;
     if (R < 1) return;
     const int TZ = 64 - 2 * T, TRp = pml.TRE - 2 * T;
     for (int s : order) {
@@ -845,6 +847,22 @@ bool adj_supported(int T, int TRE, int W)
     return adj_int_ok(sh) && pml_shape(sh, true).T >= 2;
 }
 
+// The tiles a temporally blocked launch runs on: those of the marches where
+// they were built, else the LDS tiles of the shape.
+const TileSet& fwd_set(const bhfwi_ctx* c)
+{
+    return c->fmarch.t[1].empty() ? c->ftiles : c->fmarch;
+}
+
+// xm: the optional outputs of the launch (bit 0 density, bit 1 pseudo-Hessian,
+// bit 2 wavelet record).  The extra register sums need the alternative LDS
+// shape; the wavelet record does not.
+const TileSet& adj_set(const bhfwi_ctx* c, int xm)
+{
+    if (!c->amarch.t[1].empty()) return c->amarch;
+    return (xm & 3) != 0 && adj_x_shape(c).T >= 2 ? c->xtiles : c->atiles;
+}
+
 // The PML tiles of a block run on a second stream, forked from and joined
 // back into st around the block (in a captured graph: two parallel branches),
 // so that they share the GPU with the interior tiles instead of following
@@ -949,8 +967,8 @@ void fwd_tb_launch(bhfwi_ctx* c, hipStream_t st, int n0, int nsteps, const float
                    const float* mu, const float* rho, const float* wav, const float* in,
                    float* out, float* traces, float* hist)
 {
-    const bool march = !c->fmarch.t[1].empty();
-    const TileSet& ts = march ? c->fmarch : c->ftiles;
+    const TileSet& ts = fwd_set(c);
+    const bool march = &ts == &c->fmarch;
     const int na[2] = {active_tiles(ts, 0, n0), active_tiles(ts, 1, n0)};
     if (na[0] + na[1] <= 0) return;
     EvScope ev(c, st, hist ? 1 : 0);
@@ -1010,11 +1028,8 @@ void adj_tb_launch(bhfwi_ctx* c, hipStream_t st, int n_hi, int nsteps, const flo
                    float* out, const float* hist_hi, float* acc, float* acc_rho, float* acc_h)
 {
     const int xm = (acc_rho ? 1 : 0) | (acc_h ? 2 : 0) | (c->wgrad ? 4 : 0);
-    const Shape xs = adj_x_shape(c);
-    // the extra register sums need the alternative shape; the wavelet record does not
-    const bool alt = (xm & 3) != 0 && xs.T >= 2;
-    const bool march = !c->amarch.t[1].empty();
-    const TileSet& ts = march ? c->amarch : alt ? c->xtiles : c->atiles;
+    const TileSet& ts = adj_set(c, xm);
+    const bool march = &ts == &c->amarch;
     const int n_lo = n_hi - nsteps + 1;
     const int na[2] = {active_tiles(ts, 0, n_lo), active_tiles(ts, 1, n_lo)};
     if (na[0] + na[1] <= 0) return;
@@ -1028,7 +1043,7 @@ void adj_tb_launch(bhfwi_ctx* c, hipStream_t st, int n_hi, int nsteps, const flo
                              rho, resid, in, out, hist_hi, acc, acc_rho, acc_h, xm);
             continue;
         }
-        const Shape sh = q ? ts.pml : alt ? xs : adj_shape(c);
+        const Shape sh = q ? ts.pml : &ts == &c->xtiles ? adj_x_shape(c) : adj_shape(c);
         const int T = sh.T, TRE = sh.TRE, W = sh.W;
         if (q == 0) {
             constexpr int PMV = 0;
@@ -1589,6 +1604,19 @@ int bhfwi_kernel_shapes(const bhfwi_ctx* c, int32_t* out)
         out[3 * q] = s[q].T;
         out[3 * q + 1] = s[q].TRE;
         out[3 * q + 2] = s[q].W;
+    }
+    return BHFWI_OK;
+}
+
+int bhfwi_kernel_tiles(const bhfwi_ctx* c, int32_t* out)
+{
+    if (!c || !out) return BHFWI_EINVAL;
+    const TileSet* ts[3] = {&fwd_set(c), &adj_set(c, 0), &adj_set(c, 3)};
+    for (int q = 0; q < 3; ++q) {
+        const bool march = ts[q] == &c->fmarch || ts[q] == &c->amarch;
+        out[3 * q] = march ? ts[q]->rows : 0;
+        out[3 * q + 1] = (int32_t)ts[q]->t[0].size();
+        out[3 * q + 2] = (int32_t)ts[q]->t[1].size();
     }
     return BHFWI_OK;
 }
