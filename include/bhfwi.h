@@ -87,6 +87,12 @@ typedef struct {
     int32_t work_items;       /* wave work items per time step */
 } bhfwi_sizes_t;
 
+/* Value of bhfwi_tune.adj_tb_rows with adj_tb_steps 0 and (tb_steps, tb_rows,
+ * tb_waves) = (6, 32, 16): the tune names no shapes and the library runs its own
+ * choice for the survey (bhfwi_kernel_shapes reports it).  The default of a
+ * context; any other value of those six fields names the shapes that run. */
+#define BHFWI_TB_AUTO (-1)
+
 /* Tunables of the wave-march kernels (every value in range is correct; only
  * speed changes).  rows_per_wave <= 4 selects kernels that issue all loads of
  * a wave before computing. */
@@ -118,7 +124,8 @@ typedef struct {
                                  1: radial tile fastest, and each of the 8 XCDs of
                                  the GPU walks one contiguous chunk of the table
                                  so that tiles with overlapping halos share its L2 */
-    int32_t adj_tb_steps;     /* adjoint: 0 = the forward's shape (tb_*), 1 = one
+    int32_t adj_tb_steps;     /* adjoint: 0 = the forward's shape (tb_*; with
+                                 adj_tb_rows BHFWI_TB_AUTO, see there), 1 = one
                                  step per launch (wave march), >= 2 = its own
                                  shape (adj_tb_steps, adj_tb_rows, adj_tb_waves)
                                  from the supported forward shapes except

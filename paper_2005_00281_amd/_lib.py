@@ -53,6 +53,12 @@ class Tune(C.Structure):
                 ("full_history", C.c_int32), ("fwd_tile_overlap", C.c_int32)]
 
 
+# Tune fields that name kernel shapes, and the mark (bhfwi.h) in adj_tb_rows of
+# a tune that names none.
+TB_FIELDS = ("tb_steps", "tb_rows", "tb_waves", "adj_tb_steps", "adj_tb_rows", "adj_tb_waves")
+TB_AUTO = -1
+
+
 class PlanBytes(C.Structure):
     _fields_ = [("ckpt_every", C.c_int32), ("pad_", C.c_int32), ("fwd_ws_bytes", C.c_int64),
                 ("ckpt_bytes", C.c_int64), ("adj_ws_bytes", C.c_int64), ("acc_bytes", C.c_int64),
@@ -402,7 +408,10 @@ class Survey:
     # ---------------------------------------------------------------- tuning
     def set_tune(self, **kw):
         """Change any subset of the bhfwi_tune fields (a value of None keeps
-        the current one)."""
+        the current one).  A survey runs the library's own kernel shapes until
+        a call names one of TB_FIELDS; the fields it leaves out then take the
+        values get_tune() shows (6x32x16 tiles, the adjoint as the forward).
+        adj_tb_rows=TB_AUTO, as in a default get_tune(), goes back."""
         names = [n for n, _ in Tune._fields_]
         bad = set(kw) - set(names)
         if bad:
@@ -410,6 +419,9 @@ class Survey:
         cur = Tune()
         _check(load().bhfwi_get_tune(self._h, C.byref(cur)), self._h)
         t = Tune(**{n: int(getattr(cur, n) if kw.get(n) is None else kw[n]) for n in names})
+        if (kw.get("adj_tb_rows") is None and t.adj_tb_rows == TB_AUTO and
+                any(kw.get(n) is not None for n in TB_FIELDS)):
+            t.adj_tb_rows = 0
         _check(load().bhfwi_set_tune(self._h, C.byref(t)), self._h)
         _check(load().bhfwi_sizes(self._h, C.byref(self.sizes)), self._h)
 

@@ -170,6 +170,7 @@ struct bhfwi_ctx {
     Shape f4{2, 32, 16};  // fourth-order forward time blocks (T = 0: one step per launch)
     TileSet f4tiles;      // their tiles (halo 3T)
     bhfwi_tune tune{};
+    Shape own_fwd{6, 32, 16}, own_adj{6, 32, 16};  // the library's own shapes (own_shapes)
     std::vector<int4> work;
     std::vector<int> work_nt;  // nt of each work item's shot, non-increasing
     TileSet ftiles, atiles;    // temporally blocked tiles of the forward / adjoint shape
@@ -246,9 +247,18 @@ void pml_coef(double x, double d0, double f0, double dt, float* a, float* b)
 
 Shape pml_shape(Shape sh, bool adj);
 
+// Whether a tune names no kernel shapes of its own: the default's fields with
+// the mark in a field that adj_tb_steps = 0 leaves unused.
+bool own_shapes(const bhfwi_tune& t)
+{
+    return t.adj_tb_steps == 0 && t.adj_tb_rows == BHFWI_TB_AUTO && t.tb_steps == 6 &&
+           t.tb_rows == 32 && t.tb_waves == 16;
+}
+
 Shape fwd_shape(const bhfwi_ctx* c)
 {
     const bhfwi_tune& t = c->tune;
+    if (own_shapes(t)) return c->own_fwd;
     return t.tb_steps >= 2 ? Shape{t.tb_steps, t.tb_rows, t.tb_waves} : Shape{0, 0, 0};
 }
 
@@ -257,6 +267,7 @@ Shape fwd_shape(const bhfwi_ctx* c)
 Shape adj_shape(const bhfwi_ctx* c)
 {
     const bhfwi_tune& t = c->tune;
+    if (own_shapes(t)) return c->own_adj;
     if (t.adj_tb_steps >= 2) return Shape{t.adj_tb_steps, t.adj_tb_rows, t.adj_tb_waves};
     if (t.adj_tb_steps == 1) return Shape{0, 0, 0};
     return fwd_shape(c);
@@ -537,8 +548,8 @@ int64_t count_tiles(const bhfwi_ctx* c, int T, int TRE)
     return n;
 }
 
-// Kernel shapes of a survey whose tune was never set (bhfwi_autotune refines
-// them).  The adjoint runs 6x32x16: its correlation sums are regrouped by the
+// The library's own kernel shapes, run where the tune names none
+// (bhfwi_autotune refines them).  The adjoint runs 6x32x16: its correlation sums are regrouped by the
 // steps of a block, and eight steps are no faster where they matter (12 shots
 // of 276 x 4136 cells: 85.4 ms with six, 93.5 with eight, whose marches spill).
 // The forward takes eight steps; its rows were chosen on single and batched
@@ -553,18 +564,19 @@ int64_t count_tiles(const bhfwi_ctx* c, int T, int TRE)
 //   the rest: 48 rows (2 shots of 276 x 4136: 16.9 against 18.0).
 void default_shapes(bhfwi_ctx* c)
 {
-    bhfwi_tune& t = c->tune;
-    t.tb_steps = 8;
-    t.tb_waves = 16;
-    t.adj_tb_steps = 6;
-    t.adj_tb_rows = 32;
-    t.adj_tb_waves = 16;
+    c->own_adj = Shape{6, 32, 16};
+    c->own_fwd = Shape{8, 48, 16};
     if (count_tiles(c, 8, 32) <= c->ncu)
-        t.tb_rows = 32;
-    else if (count_tiles(c, 8, 48) <= c->ncu || march_rows(c, 8))
-        t.tb_rows = 48;
-    else
-        t.tb_rows = 2 * count_tiles(c, 8, 64) <= 3 * (int64_t)c->ncu ? 64 : 48;
+        c->own_fwd.TRE = 32;
+    else if (count_tiles(c, 8, 48) > c->ncu && !march_rows(c, 8) &&
+             2 * count_tiles(c, 8, 64) <= 3 * (int64_t)c->ncu)
+        c->own_fwd.TRE = 64;
+    bhfwi_tune& t = c->tune;
+    t.tb_steps = 6;
+    t.tb_rows = 32;
+    t.tb_waves = 16;
+    t.adj_tb_steps = t.adj_tb_waves = 0;
+    t.adj_tb_rows = BHFWI_TB_AUTO;
 }
 
 int active_items(const bhfwi_ctx* c, int n)
@@ -905,7 +917,7 @@ void fwd_march_launch(bhfwi_ctx* c, hipStream_t st, const TileSet& ts, int na, i
                       const float* lam, const float* mu, const float* rho, const float* wav,
                       const float* in, float* out, float* traces, float* hist)
 {
-    const int tz = 64 - 2 * c->tune.tb_steps;
+    const int tz = 64 - 2 * fwd_shape(c).T;
 #define BHFWI_MF(TT, HH)                                                                      \
     hipLaunchKernelGGL((bhfwi::march::k_fwd_march<TT, HH>), dim3(na), dim3(64), 0, st,        \
                        c->d_shots, ts.d[0], na, c->tune.tile_map, tz, n0, lam, mu, rho, wav,  \
@@ -1542,6 +1554,7 @@ int bhfwi_set_tune(bhfwi_ctx* c, const bhfwi_tune* t)
     HIPOK(c, hipDeviceSynchronize());  // no replay may still read the old work table
     clear_graphs(c);
     c->tune = *t;
+    if (t->adj_tb_rows == BHFWI_TB_AUTO && !own_shapes(*t)) c->tune.adj_tb_rows = 0;
     rebuild_work(c);
     return upload_work(c);
 }
@@ -1641,7 +1654,8 @@ int bhfwi_autotune(bhfwi_ctx* c, void* stream, const float* lam, const float* mu
     if (adj_ws_bytes < (2 * c->ast_len + 2 * (int64_t)P * c->cells) * (int64_t)sizeof(float))
         return fail(c, BHFWI_ENOMEM, "autotune: adj_ws holds no history for %d probe steps "
                                      "(tune with full_history 0)", P);
-    const bhfwi_tune base = c->tune;
+    bhfwi_tune base = c->tune;
+    if (base.adj_tb_rows == BHFWI_TB_AUTO) base.adj_tb_rows = 0;  // every candidate names shapes
     float* fb[2] = {(float*)fwd_ws, (float*)fwd_ws + c->fst_len};
     float* ab[2] = {(float*)adj_ws, (float*)adj_ws + c->ast_len};
     float* hist = (float*)adj_ws + 2 * c->ast_len;
