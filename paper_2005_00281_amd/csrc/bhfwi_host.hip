@@ -538,39 +538,62 @@ int default_rows(const bhfwi_ctx* c)
     return (int)std::max<int64_t>(4, std::min<int64_t>(64, r));
 }
 
-// Tiles of the temporally blocked shape (T, TRE, .) over every shot.
-int64_t count_tiles(const bhfwi_ctx* c, int T, int TRE)
+// The forward shapes the library chooses from, with the times in microseconds
+// that a block of T steps takes on one MI355X: per launch, per round of
+// interior workgroups (two share a compute unit where the kernel's registers
+// allow it, and a round that leaves one to each is shorter) and per round of PML
+// workgroups (one per compute unit).  Least squares over 70 surveys of 1 to 16
+// shots of 68 x 240 to 1000 x 6240 cells, with and without the one-launch blocks:
+// rms error 3 to 4 %.
+struct FwdCost {
+    Shape sh;
+    int per_cu;
+    double launch, half, full, pml;
+};
+constexpr FwdCost kFwdCost[] = {{{6, 32, 16}, 2, 3.6, 7.1, 10.8, 9.2},
+                                {{8, 32, 16}, 2, 4.0, 7.2, 11.5, 10.3},
+                                {{8, 48, 16}, 2, 4.4, 10.8, 17.2, 14.9},
+                                {{8, 64, 16}, 1, 2.0, 17.1, 17.1, 11.2}};
+
+// Time of one block of shape f over every shot, from the tiles that would run.
+double block_time(const bhfwi_ctx* c, const std::vector<int>& order, const FwdCost& f)
 {
-    int64_t n = 0;
-    for (const ShotDev& S : c->sd)
-        n += (int64_t)((S.NZ + 63 - 2 * T) / (64 - 2 * T)) *
-             ((S.NR + TRE - 2 * T - 1) / (TRE - 2 * T));
-    return n;
+    TileSet ts;
+    build_tiles(c, order, f.sh, pml_shape(f.sh, false), &ts);
+    const int n = (int)ts.t[0].size(), p = (int)ts.t[1].size();
+    const int slots = f.per_cu * c->ncu, rest = n % slots;
+    return f.launch * ((n > 0) + (p > 0)) + f.full * (n / slots + (rest > c->ncu)) +
+           f.half * (rest > 0 && rest <= c->ncu) + f.pml * ((p + c->ncu - 1) / c->ncu);
 }
 
 // The library's own kernel shapes, run where the tune names none
-// (bhfwi_autotune refines them).  The adjoint runs 6x32x16: its correlation sums are regrouped by the
-// steps of a block, and eight steps are no faster where they matter (12 shots
-// of 276 x 4136 cells: 85.4 ms with six, 93.5 with eight, whose marches spill).
-// The forward takes eight steps; its rows were chosen on single and batched
-// gradients (ms, against 6x32x16 in both directions):
-//   tiles that fit the GPU in one round run in one launch per block, on 32 rows
-//     (148 x 552 cells, 1000 steps: 6.9 against 13.7) or 48 (220 x 1540, 400
-//     steps: 4.9 against 6.5);
-//   enough columns for the marches: 48-row PML tiles (8 shots of 276 x 4136,
-//     400 steps: 59.5 against 70.0);
-//   one and a half rounds of 64-row tiles, whose interior ones fit in one
-//     (340 x 2088, 400 steps: 7.5 against 8.7);
-//   the rest: 48 rows (2 shots of 276 x 4136: 16.9 against 18.0).
+// (bhfwi_autotune refines them).  The adjoint runs 6x32x16: its correlation sums are
+// regrouped by the steps of a block, and eight steps are no faster where they
+// matter (12 shots of 276 x 4136 cells: 85.4 ms with six, 93.5 with eight, whose
+// marches spill).  The forward runs 48-row PML tiles beside its marches (8 shots
+// of 276 x 4136 cells, 250 steps: 7.5 ms; 8.1 with 32 rows); other surveys take the
+// shape of the least time per step above: modelling on those 70 within 4 % of the
+// best of the four, and on 60 more a gradient at most 2 % slower than on 6x32x16.
+// The number of tiles alone does not tell (modelling, 250 steps: 4 shots of
+// 70 x 3040 cells 1.59 ms with 6x32 and 2.09 with 8x48; 8 of 148 x 552 cells
+// 1.30 with 8x32 and 1.71 with 8x64; 10 of 70 x 760 cells 1.41 with 8x64 and
+// 1.52 with 6x32).
 void default_shapes(bhfwi_ctx* c)
 {
     c->own_adj = Shape{6, 32, 16};
     c->own_fwd = Shape{8, 48, 16};
-    if (count_tiles(c, 8, 32) <= c->ncu)
-        c->own_fwd.TRE = 32;
-    else if (count_tiles(c, 8, 48) > c->ncu && !march_rows(c, 8) &&
-             2 * count_tiles(c, 8, 64) <= 3 * (int64_t)c->ncu)
-        c->own_fwd.TRE = 64;
+    if (!march_rows(c, 8)) {
+        std::vector<int> order(c->nshot);
+        for (int s = 0; s < c->nshot; ++s) order[s] = s;
+        double best = 0;
+        for (const FwdCost& f : kFwdCost) {
+            const double t = block_time(c, order, f) / f.sh.T;
+            if (!best || t < best) {
+                best = t;
+                c->own_fwd = f.sh;
+            }
+        }
+    }
     bhfwi_tune& t = c->tune;
     t.tb_steps = 6;
     t.tb_rows = 32;

@@ -71,3 +71,30 @@ def test_autotuned_shapes_are_named():
     assert fwd[0] == (t["tb_steps"] if t["tb_steps"] >= 2 else 0)
     if t["adj_tb_steps"] >= 2:
         assert adj == (t["adj_tb_steps"], t["adj_tb_rows"], t["adj_tb_waves"])
+
+
+@pytest.mark.parametrize("size,fwd", [
+    # the shapes measured fastest (forward ms of 250 steps, this shape against
+    # the one a count of whole columns chose)
+    ((4, 50, 3000), (6, 32, 16)),   # 1.59 against 2.09 on 8x48
+    ((8, 128, 512), (8, 32, 16)),   # 1.30 against 1.71 on 8x64
+    ((1, 48, 6000), (6, 32, 16)),   # 0.97 against 1.10 on 8x48
+    ((1, 70, 5565), (8, 48, 16)),   # 1.09 against 1.38 on 8x64
+    ((1, 176, 3391), (6, 32, 16)),  # 1.15 against 1.38 on 8x64
+    ((10, 148, 267), (8, 32, 16)),  # 1.30 against 1.65 on 8x64
+    ((10, 50, 720), (8, 64, 16)),   # 1.41 against 1.52 on 6x32: thin, in PML tiles only
+    ((1, 128, 512), (8, 32, 16)),   # one launch per block
+    ((8, 256, 4096), (8, 48, 16))])  # beside the marches
+def test_own_forward_shape(size, fwd):
+    import paper_2005_00281_amd as P
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the shapes were measured on 256 compute units")
+    print("[case] own shape", size, flush=True)
+    n, nr, nz = size
+    one = workloads.tiny(nr=24, nz=48, nt=40).shots[0]
+    sh = workloads.Shot(nr, nz, 20, 20, one.dr, one.dz, one.dt, 40, one.f0, one.vmax, 25,
+                        one.rec_k, one.wavelet)
+    sv = P.Survey([sh] * n, (nr + 20, nz + 40), ckpt_every=20)
+    assert _shapes(sv) == (fwd, (6, 32, 16))
