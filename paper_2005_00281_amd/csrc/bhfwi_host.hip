@@ -387,6 +387,12 @@ int clear_columns(const ShotDev& S, int T)
     return n;
 }
 
+// Most steps per launch of the marches.  An adjoint march of eight spills 41 to
+// 96 VGPRs: 12 shots of 276 x 4136 cells, 192 adjoint steps with the stored
+// history, 29.3 ms, against 20.4 on 8x32 LDS tiles, 23.3 on 8x64 (and 18.2 in
+// marches of six); with the density and pseudo-Hessian sums 52.9 against 29.6.
+constexpr int kFwdMarch = 8, kAdjMarch = 6;
+
 // Radial rows per tile of the march kernels with T steps per launch, or 0
 // where the LDS tiles run.  A wave issues a vector instruction every other
 // slot of its SIMD, so the marches need two waves per SIMD (8 per compute
@@ -429,20 +435,20 @@ int march_rows(const bhfwi_ctx* c, int T)
     return best;
 }
 
-// Tiles of the march kernels with T steps per launch.  In a column clear of
-// the axial PML, the rows whose skewed window stays below the radial layer are
+// Tiles of the march kernels with T steps per launch; the adjoint has marches
+// of up to six (kAdjMarch).  In a column clear of the axial PML, the rows whose skewed window stays below the radial layer are
 // cut into equal tiles of at most R rows (list 0: shot, first owned axial row,
 // radial rows [z, w)); the rest of the column, and every column that reaches
 // an axial layer, into the LDS tiles of shape pml (list 1).
 void build_march(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Shape pml,
-                 TileSet* ts)
+                 int most, TileSet* ts)
 {
     for (int q = 0; q < 2; ++q) {
         ts->t[q].clear();
         ts->nt[q].clear();
     }
     ts->pml = pml;
-    const int T = sh.T, R = march_rows(c, T);
+    const int T = sh.T, R = T <= most ? march_rows(c, T) : 0;
     ts->rows = R;
     if (R < 1) return;
     const int TZ = 64 - 2 * T, TRp = pml.TRE - 2 * T;
@@ -503,8 +509,8 @@ void rebuild_work(bhfwi_ctx* c)
     build_tiles(c, order, fs, pml_shape(fs, false), &c->ftiles, c->tune.fwd_tile_overlap != 0);
     build_tiles(c, order, as, pml_shape(as, true), &c->atiles);
     build_tiles(c, order, xs, pml_shape(xs, true), &c->xtiles);
-    build_march(c, order, fs, pml_shape(fs, false), &c->fmarch);
-    build_march(c, order, as, pml_shape(as, true), &c->amarch);
+    build_march(c, order, fs, pml_shape(fs, false), kFwdMarch, &c->fmarch);
+    build_march(c, order, as, pml_shape(as, true), kAdjMarch, &c->amarch);
     // fourth-order forward blocks: a three-cell halo per step, one shape for
     // the interior and the PML tiles
     const Shape h4{3 * c->f4.T, c->f4.TRE, c->f4.W};
@@ -569,8 +575,7 @@ double block_time(const bhfwi_ctx* c, const std::vector<int>& order, const FwdCo
 // The library's own kernel shapes, run where the tune names none
 // (bhfwi_autotune refines them).  The adjoint runs 6x32x16: its correlation sums are
 // regrouped by the steps of a block, and eight steps are no faster where they
-// matter (12 shots of 276 x 4136 cells: 85.4 ms with six, 93.5 with eight, whose
-// marches spill).  The forward runs 48-row PML tiles beside its marches (8 shots
+// matter (kAdjMarch).  The forward runs 48-row PML tiles beside its marches (8 shots
 // of 276 x 4136 cells, 250 steps: 7.5 ms; 8.1 with 32 rows); other surveys take the
 // shape of the least time per step above: modelling on those 70 within 4 % of the
 // best of the four, and on 60 more a gradient at most 2 % slower than on 6x32x16.
@@ -932,7 +937,8 @@ struct PmlFork {
 
 // Steps per launch of the march kernels (a remainder of a block runs the
 // kernel of its own length on the same tiles).
-#define BHFWI_MARCH(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+#define BHFWI_MARCH_ADJ(X) X(1) X(2) X(3) X(4) X(5) X(6)
+#define BHFWI_MARCH(X) BHFWI_MARCH_ADJ(X) X(7) X(8)
 
 // The nsteps (<= T) steps from step n0 of a block on its interior tiles (na of
 // them in ts), by the forward march.
@@ -980,7 +986,7 @@ void adj_march_launch(bhfwi_ctx* c, hipStream_t st, const TileSet& ts, int na, i
         default: BHFWI_MA(TT, 0); break;     \
         }                                    \
         break;
-    switch (nsteps) { BHFWI_MARCH(BHFWI_ML) }
+    switch (nsteps) { BHFWI_MARCH_ADJ(BHFWI_ML) }
 #undef BHFWI_ML
 #undef BHFWI_MA
 }

@@ -19,8 +19,8 @@
 // What bounds it: memory (4.27 TB/s of HBM traffic where a copy moves 5.0; 8 of
 // 92 B per cell-step are the stored velocities, which no blocking saves) and,
 // next, vector issue.  12 shots of 276 x 4136 cells, 1250 steps: gradient 265.1
-// ms, 315.7 with all tiles in LDS.  T = 8 spills (93.5 ms for 400 steps, 85.4 at
-// T = 6).
+// ms, 315.7 with all tiles in LDS.  T = 8 spills and is not built: an adjoint of
+// eight steps per launch keeps its LDS tiles.
 //
 // X selects the optional outputs of bhfwi_tb_adj.hip: bit 0 the density
 // correlation, bit 1 the pseudo-Hessian diagonal, bit 2 the wavelet record.

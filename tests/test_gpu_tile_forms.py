@@ -182,3 +182,17 @@ def test_one_launch_and_one_step_report_their_tiles():
         assert sv.kernel_tiles()[part][:2] == (0, 0) and sv.kernel_tiles()[part][2] > 0
     sv.set_tune(tb_steps=0, adj_tb_steps=1)
     assert set(sv.kernel_tiles().values()) == {(0, 0, 0)}
+
+
+@pytest.mark.parametrize("rows", [32, 48, 64])
+def test_eight_step_adjoints_keep_their_lds_tiles(rows):
+    """An adjoint of eight steps per launch has no march (it would spill): a
+    survey whose forward marches runs it on the LDS tiles of its shape."""
+    print("[case] eight-step adjoint, rows", rows, flush=True)
+    c = _Check(_batch([(150, 288)] * 300, 200), (0, 299))
+    sv = c.survey(**dict(MID, adj_tb_steps=8, adj_tb_rows=rows))
+    tiles = sv.kernel_tiles()
+    assert tiles["fwd"][0] >= 64
+    for part in ("adj", "adj_x"):
+        assert tiles[part][0] == 0 and tiles[part][1] > 0 and tiles[part][2] > 0
+    c.run()
