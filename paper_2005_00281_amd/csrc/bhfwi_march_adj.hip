@@ -203,6 +203,7 @@ k_adj_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
                 a_hm = ldrow(acc_h + S.cell_off + cells_total, co);
             }
         }
+        const int sn = min(s + 1, send);  // the last step fetches its own rows again
         asm volatile("" : "+s"(hstr));  // history rows are addressed as they come
         __builtin_amdgcn_sched_barrier(0);
         auto ring = [&](int r) {
@@ -219,7 +220,7 @@ k_adj_march(const ShotDev* __restrict__ shots, const int4* __restrict__ work, in
             const Coef c = nx;
             nx = ring(q);  // row q: this level's old row, the next level's new one
             const float vr1 = pvr[t], vz0 = pvz[t];
-            fetch_hist(s + 1, t, GENC);
+            fetch_hist(sn, t, GENC);
             __builtin_amdgcn_sched_barrier(0);
             const float rR = rRs[t], rRq = rRs[t + 1], rZr = rZs[t], rZ = rZs[t + 1];
             // A: residual, drivers of the transposed stress update at row r

@@ -24,16 +24,18 @@ def _f32(a):
     return torch.as_tensor(np.ascontiguousarray(a, np.float32), device=_dev())
 
 
-def _batch(sizes, nt, pml=6):
+def _batch(sizes, nt, pml=6, pr=None):
     """Shots of the given (nr, nz) over one small model, windows shifted by one
-    axial row each; every third record ends inside a time block."""
+    axial row each; every third record ends inside a time block.  pr: rows of
+    the radial layer where they are not those of the axial layers."""
+    pr = pml if pr is None else pr
     nr, nz = max(r for r, _ in sizes), max(z + s for s, (_, z) in enumerate(sizes))
     w = workloads.tiny(nr=nr, nz=nz, p=pml, nt=nt, dt=0.75e-6)
     shots = []
     for s, (r, z) in enumerate(sizes):
         one = workloads.tiny(nr=r, nz=z, p=pml, nt=nt, dt=0.75e-6).shots[0]
         n = nt if s % 3 else nt - 3
-        shots.append(workloads.Shot(r, z, pml, pml, one.dr, one.dz, one.dt, n, one.f0,
+        shots.append(workloads.Shot(r, z, pr, pml, one.dr, one.dz, one.dt, n, one.f0,
                                     w.shots[0].vmax, one.src_k, one.rec_k, one.wavelet[:n], s))
     w.shots = shots
     return w
@@ -196,3 +198,16 @@ def test_eight_step_adjoints_keep_their_lds_tiles(rows):
     for part in ("adj", "adj_x"):
         assert tiles[part][0] == 0 and tiles[part][1] > 0 and tiles[part][2] > 0
     c.run()
+
+
+@pytest.mark.parametrize("pml", [6, 0])
+def test_marches_without_a_radial_layer(pml):
+    """Without a radial layer the march's last row is the grid's: what the last
+    step of a column fetches ahead must stay on it.  With and without axial
+    layers; the record holds the way to that row and back."""
+    print("[case] marches, no radial layer, axial", pml, flush=True)
+    c = _Check(_batch([(150, 288)] * 300, 640, pml=pml, pr=0), (0, 299))
+    sv = c.survey(**MID)
+    tiles = sv.kernel_tiles()
+    assert tiles["fwd"][0] >= 64 and tiles["adj"][0] >= 64
+    c.run([slice(138, 150)])
