@@ -21,7 +21,9 @@
 // prefix arrays are padded by one double in nine, because the scan reads eight
 // consecutive doubles per lane.  64 gathers of 13 x 16000 samples, 560
 // slownesses, with the picks of P and S: 5.7 ms; 12.9 ms with the receivers
-// innermost, tests per read and an unpadded scan.
+// innermost, tests per read and an unpadded scan.  A span of fewer samples forms
+// one, two or four per thread: 64 gathers of 13 x 400 samples, 560 slownesses,
+// windows of 200: 246 us, 596 us with all eight formed for every span.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -47,6 +49,63 @@ __device__ __forceinline__ double sem_wave_scan(double v, int lane)
         if (lane >= o) v += u;
     }
     return v;
+}
+
+// Squared stack and energy of samples n_lo .. n_lo + len - 1, len <= N
+// kSemThreads, N of them per thread.
+template <int N>
+__device__ __forceinline__ void sem_stack(const float* __restrict__ x, int nrec, int nt, int n_lo,
+                                          int len, const int* Lq, const float* Lf, double* Ps,
+                                          double* Pe)
+{
+    static_assert(N <= kSemPer, "more samples than are staged");
+    const int tid = threadIdx.x;
+    float st[N], en[N];  // samples n_lo + tid + r kSemThreads
+#pragma unroll
+    for (int r = 0; r < N; ++r) st[r] = en[r] = 0.f;
+    for (int m = 0; m < nrec; ++m) {
+        const int q0 = __builtin_amdgcn_readfirstlane(Lq[m]);
+        const float f = __builtin_bit_cast(
+            float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, Lf[m])));
+        const float* __restrict__ xm = x + (long long)m * nt;
+        const long long first = (long long)n_lo + q0;  // sample read for n_lo
+        if (first >= 0 && first + N * kSemThreads < nt) {  // uniform: all reads in the record
+            const float* __restrict__ xr = xm + first;
+            float a[N], b[N];
+#pragma unroll
+            for (int r = 0; r < N; ++r) {
+                a[r] = xr[tid + r * kSemThreads];
+                b[r] = xr[tid + r * kSemThreads + 1];
+            }
+#pragma unroll
+            for (int r = 0; r < N; ++r) {
+                const float v = a[r] + f * (b[r] - a[r]);
+                st[r] += v;
+                en[r] += v * v;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < N; ++r) {
+                // sample at or before the shifted time
+                const long long q = first + tid + r * kSemThreads;
+                const float a = (q >= 0 && q < nt) ? xm[q] : 0.f;
+                const float b = (q + 1 >= 0 && q + 1 < nt) ? xm[q + 1] : 0.f;
+                // the shifted time lies inside the record, or at its last sample
+                float v = 0.f;
+                if (q >= 0 && (q < nt - 1 || (q == nt - 1 && f == 0.f))) v = a + f * (b - a);
+                st[r] += v;
+                en[r] += v * v;
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        const int k = tid + r * kSemThreads + 1;
+        if (k <= len) {
+            Ps[sem_at(k)] = (double)st[r] * st[r];
+            Pe[sem_at(k)] = en[r];
+        }
+    }
 }
 
 __global__ void __launch_bounds__(kSemThreads, 4)
@@ -80,52 +139,16 @@ k_semblance(int nrec, int nt, const float* __restrict__ traces, float dt,
     const int n_lo = i0 * stride;
     const int n_hi = min((i1 - 1) * stride + win, n_lo + kSemSpan);
     const int len = n_hi - n_lo;
-    float st[kSemPer], en[kSemPer];  // samples n_lo + tid + r kSemThreads
-#pragma unroll
-    for (int r = 0; r < kSemPer; ++r) st[r] = en[r] = 0.f;
-    for (int m = 0; m < nrec; ++m) {
-        const int q0 = __builtin_amdgcn_readfirstlane(Lq[m]);
-        const float f = __builtin_bit_cast(
-            float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, Lf[m])));
-        const float* __restrict__ xm = x + (long long)m * nt;
-        const long long first = (long long)n_lo + q0;  // sample read for n_lo
-        if (first >= 0 && first + kSemSpan < nt) {  // uniform: every read inside the record
-            const float* __restrict__ xr = xm + first;
-            float a[kSemPer], b[kSemPer];
-#pragma unroll
-            for (int r = 0; r < kSemPer; ++r) {
-                a[r] = xr[tid + r * kSemThreads];
-                b[r] = xr[tid + r * kSemThreads + 1];
-            }
-#pragma unroll
-            for (int r = 0; r < kSemPer; ++r) {
-                const float v = a[r] + f * (b[r] - a[r]);
-                st[r] += v;
-                en[r] += v * v;
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < kSemPer; ++r) {
-                // sample at or before the shifted time
-                const long long q = first + tid + r * kSemThreads;
-                const float a = (q >= 0 && q < nt) ? xm[q] : 0.f;
-                const float b = (q + 1 >= 0 && q + 1 < nt) ? xm[q + 1] : 0.f;
-                // the shifted time lies inside the record, or at its last sample
-                float v = 0.f;
-                if (q >= 0 && (q < nt - 1 || (q == nt - 1 && f == 0.f))) v = a + f * (b - a);
-                st[r] += v;
-                en[r] += v * v;
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kSemPer; ++r) {
-        const int k = tid + r * kSemThreads + 1;
-        if (k <= len) {
-            Ps[sem_at(k)] = (double)st[r] * st[r];
-            Pe[sem_at(k)] = en[r];
-        }
-    }
+    // only the samples of the span: a short one (few windows, the end of a record)
+    // fills a part of the workgroup's rows of kSemThreads samples
+    if (len > 4 * kSemThreads)
+        sem_stack<8>(x, nrec, nt, n_lo, len, Lq, Lf, Ps, Pe);
+    else if (len > 2 * kSemThreads)
+        sem_stack<4>(x, nrec, nt, n_lo, len, Lq, Lf, Ps, Pe);
+    else if (len > kSemThreads)
+        sem_stack<2>(x, nrec, nt, n_lo, len, Lq, Lf, Ps, Pe);
+    else
+        sem_stack<1>(x, nrec, nt, n_lo, len, Lq, Lf, Ps, Pe);
     __syncthreads();
     // prefix sums in double: each thread totals kSemPer consecutive samples,
     // the totals are scanned over the workgroup, then each thread turns its own
