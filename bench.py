@@ -59,8 +59,8 @@ ADJ_BLOCK_BYTES_PER_CELL_X = 16
 # a device copy of 1 GiB reads 1.000 GiB and writes 1.000 GiB on them,
 # profiles/copy_calibration.md), the mean per dispatch summed over the
 # interior and PML kernels of one block.  An entry holds only for the kernel
-# sources it was measured on (SHA-256 of PMC_SOURCES: the adjoint block kernel
-# and the device code it includes), the same shapes, tile map and workload;
+# sources it was measured on (SHA-256 of PMC_SOURCES: the adjoint block kernels
+# and the device code they include), the same kernels, tile map and workload;
 # otherwise traffic is null.
 PMC_SOURCES = ("paper_2005_00281_amd/csrc/bhfwi_march_adj.hip",
                "paper_2005_00281_amd/csrc/bhfwi_march_fwd.hip",
@@ -70,16 +70,16 @@ PMC_SOURCES = ("paper_2005_00281_amd/csrc/bhfwi_march_adj.hip",
                "paper_2005_00281_amd/csrc/bhfwi_internal.h")
 PMC_TRAFFIC = {
     # (kernel, tile_map, workload, sources sha256[:16]): (read bytes, write bytes)
-    ("k_adj_tb<6, 32, 16, 0, 0> + k_adj_tb<6, 32, 16, 1, 0>", 1, "c3", "f361bc00e3e764f0"):
-        (8127040826, 3470398762),
+    ("k_adj_march<6, 0> + k_adj_tb<6, 32, 16, 1, 0>", 1, "c3", "cb2f412307e60d5f"):
+        (8618724128, 3261307152),
 }
 
 # Vector instructions of the same adjoint block, from a rocprofv3 --pmc run
 # of the same command with SQ_INSTS_VALU (wave64 instructions, summed over the
 # interior and PML kernels of one block, mean per dispatch); the same keys.
 PMC_VALU = {
-    ("k_adj_tb<6, 32, 16, 0, 0> + k_adj_tb<6, 32, 16, 1, 0>", 1, "c3", "f361bc00e3e764f0"):
-        1202725870,
+    ("k_adj_march<6, 0> + k_adj_tb<6, 32, 16, 1, 0>", 1, "c3", "cb2f412307e60d5f"):
+        943991529,
 }
 
 # temporally blocked shapes (T, tile rows incl. halo, waves) of both kernels,
@@ -103,6 +103,19 @@ def adj_shape(tune):
     if tune["adj_tb_steps"] == 1:
         return (0, 0, 0)
     return (tune["tb_steps"], tune["tb_rows"], tune["tb_waves"])
+
+
+def adjoint_kernels(ka, kp, tiles, xm, rows_per_wave):
+    """Name of the kernels one second-order adjoint block runs: ka, kp the
+    shapes of the tiles clear of the PML and of the PML tiles, tiles the form
+    and the counts (Survey.kernel_tiles), xm the extra outputs."""
+    if ka[0] < 2:
+        return "k_adj_step<%d>" % (rows_per_wave if rows_per_wave <= 4 else 0)
+    march, clear, _ = tiles
+    pml = "k_adj_tb<%d, %d, %d, 1, %d>" % (kp + (xm,))
+    if march:
+        return "k_adj_march<%d, %d> + %s" % (ka[0], xm, pml)
+    return ("k_adj_tb<%d, %d, %d, 0, %d> + " % (ka + (xm,)) if clear else "") + pml
 
 
 def kernel_sources_sha():
@@ -693,13 +706,12 @@ def kernel_roofline(args, inv, surveys, tune, full):
     b4 = sv.order4_blocks
     T = (ka[0] if (args.order == 2 and ka[0] >= 2) else
          b4[0] if (args.order == 4 and b4[0] >= 2) else 1)
-    kname = (("k_adj4_tb<%d, %d, %d, 0, %d> + k_adj4_tb<%d, %d, %d, 1, %d>" % (
-              b4 + (xm,) + b4 + (xm,)) if b4[0] >= 2 else "k_adj4<%d>" % xm) if args.order == 4
-             else "k_adj_march<%d, %d> (k_adj_tb<%d, %d, %d, 0, %d> where the survey is too "
-                  "small for the marches) + k_adj_tb<%d, %d, %d, 1, %d>" % (
-             (ka[0], xm) + ka + (xm,) + kp + (xm,))
-             if ka[0] >= 2
-             else "k_adj_step<%d>" % (tune["rows_per_wave"] if tune["rows_per_wave"] <= 4 else 0))
+    tiles = sv.kernel_tiles()["adj_x" if xm else "adj"]
+    if args.order == 4:
+        kname = "k_adj4<%d>" % xm if b4[0] < 2 else " + ".join(
+            "k_adj4_tb<%d, %d, %d, %d, %d>" % (b4 + (pm, xm)) for pm in (0, 1) if tiles[1 + pm])
+    else:
+        kname = adjoint_kernels(ka, kp, tiles, xm, tune["rows_per_wave"])
     adj_avg_s = adj_ms * 1e-3 / adj_n
     # algorithmic bytes of the blocked adjoint over the timed groups: per cell
     # and launch the state, model and accumulators, per cell and step the
@@ -742,7 +754,7 @@ def kernel_roofline(args, inv, surveys, tune, full):
                 "effective_frac": round(eff_GBs / HBM_PEAK_GBS, 4),
                 "effective_model": "%d B per cell-step, unblocked" % ADJ_BYTES_PER_CELL_STEP}
     valu = PMC_VALU.get(pmc_key)
-    if valu is not None:  # the resource that bounds these kernels: vector issue
+    if valu is not None:  # the second resource these kernels lean on: vector issue
         gips = valu / adj_avg_s / 1e9
         roofline["valu"] = {"bound": "alu", "achieved": round(gips, 1),
                             "peak": VALU_PEAK_GIPS, "unit": "G wave64 VALU instructions/s",

@@ -138,7 +138,10 @@ typedef struct {
     int32_t pml_overlap;      /* 1: the PML tiles of a time block run on a second
                                  stream alongside the interior tiles (forked and
                                  joined around the block); 0 (default): after
-                                 them on the caller's stream */
+                                 them on the caller's stream, except beside the
+                                 register marches (bhfwi_kernel_tiles), whose PML
+                                 tiles take the second stream in either case,
+                                 unless rec_overlap is on */
     int32_t rec_overlap;      /* 1: bhfwi_adjoint_model recomputes checkpoint
                                  segment j-1 on a second stream while the adjoint
                                  of segment j runs (two velocity histories:
@@ -164,6 +167,8 @@ typedef struct {
                                  cover fewer rows; pays on launches of many rounds of
                                  workgroups.  0 (default): interior tiles stop
                                  at the first one whose halo reaches the layer.
+                                 No effect where the tiles clear of the PML are
+                                 register marches: their rows end there anyway.
                                  Traces and gradients differ from 0 only by FP32
                                  rounding (rows move between the interior and
                                  the PML kernel). */
@@ -281,8 +286,8 @@ int bhfwi_plan(const bhfwi_shot *shots, int32_t nshot, int64_t budget_bytes,
  * all in the PML kernel: bhfwi_kernel_tiles says which. */
 int bhfwi_kernel_shapes(const bhfwi_ctx *ctx, int32_t *out);
 
-/* The tiles those kernels run on (second order), 9 int32 to out (host): for
- * the forward, the adjoint and the adjoint with extra outputs each
+/* The tiles those kernels run on (at order 4 those of its time blocks), 9 int32
+ * to out (host): for the forward, the adjoint and the adjoint with extra outputs each
  * (m, clear, pml).  m > 0: the tiles clear of the PML are register marches of
  * at most m radial rows; m = 0: they are LDS tiles.  clear: number of those
  * tiles; pml: number of tiles the kernel with the PML memories runs (all of

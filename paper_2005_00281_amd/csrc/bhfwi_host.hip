@@ -906,7 +906,12 @@ const TileSet& adj_set(const bhfwi_ctx* c, int xm)
 // The PML tiles of a block run on a second stream, forked from and joined
 // back into st around the block (in a captured graph: two parallel branches),
 // so that they share the GPU with the interior tiles instead of following
-// them.  Returns the stream for list q.
+// them: where the tune asks for it, and always beside the marches, whose waves
+// leave room for them (192 steps, forward and adjoint, against one stream: 12
+// shots of 276 x 4136 cells 8.07 and 18.2 ms against 8.59 and 18.6; 24 of
+// 100 x 4040 cells 7.04 and 16.6 against 7.31 and 16.9), but for the overlapped
+// recompute, which would share the second stream with the adjoint.  Returns
+// the stream for list q.
 struct PmlFork {
     bhfwi_ctx* c;
     hipStream_t st;
@@ -1382,7 +1387,7 @@ int bhfwi_create(bhfwi_ctx** out, int32_t hip_device, const bhfwi_shot* shots, i
     c->tune.time_kernels = 0;
     default_shapes(c);
     c->tune.tile_map = 1;
-    c->tune.pml_overlap = 0;  // measured: concurrent PML tiles crowd out interior ones
+    c->tune.pml_overlap = 0;  // LDS tiles: concurrent PML workgroups crowd out interior ones
     c->tune.fwd_tile_overlap = 0;
     rebuild_work(c);
 
@@ -1654,6 +1659,7 @@ int bhfwi_kernel_tiles(const bhfwi_ctx* c, int32_t* out)
 {
     if (!c || !out) return BHFWI_EINVAL;
     const TileSet* ts[3] = {&fwd_set(c), &adj_set(c, 0), &adj_set(c, 3)};
+    if (c->order == 4) ts[0] = ts[1] = ts[2] = &c->f4tiles;
     for (int q = 0; q < 3; ++q) {
         const bool march = ts[q] == &c->fmarch || ts[q] == &c->amarch;
         out[3 * q] = march ? ts[q]->rows : 0;

@@ -16,11 +16,15 @@
 // leaves the last level.  The stored velocities of the next march step are
 // fetched one step ahead.
 //
-// What bounds it: memory (4.27 TB/s of HBM traffic where a copy moves 5.0; 8 of
-// 92 B per cell-step are the stored velocities, which no blocking saves) and,
-// next, vector issue.  12 shots of 276 x 4136 cells, 1250 steps: gradient 265.1
-// ms, 315.7 with all tiles in LDS.  T = 8 spills and is not built: an adjoint of
-// eight steps per launch keeps its LDS tiles.
+// What bounds it: memory.  64 shots of 276 x 4136 cells, six steps, beside the PML
+// tiles: 10.3 GB in 1887 us (5.5 TB/s, three quarters of it reads; a copy moves
+// 5.0) and 693e6 wave instructions (0.60 of one per compute unit and clock); 8 of
+// the 92 B per cell-step are the stored velocities, which no blocking saves.  The
+// PML tiles beside it end some 780 us later and bound the block.  12 of those
+// shots, 1250 steps: gradient 265.1 ms, 315.7 with all tiles in LDS.  Over 39
+// surveys the adjoint was 1.05 times as fast as on LDS tiles of six steps, from
+// 0.93 (19 shots of 211 x 2417 cells) to 1.17.  T = 8 spills and is not built: an
+// adjoint of eight steps per launch keeps its LDS tiles.
 //
 // X selects the optional outputs of bhfwi_tb_adj.hip: bit 0 the density
 // correlation, bit 1 the pseudo-Hessian diagonal, bit 2 the wavelet record.

@@ -61,6 +61,18 @@ def test_adj_shape():
     assert bench.adj_shape(dict(tune, adj_tb_steps=0)) == (8, 48, 16)
 
 
+def test_adjoint_kernels_names_what_runs():
+    # marches beside PML tiles, two LDS kernels, one launch per block, one step
+    ka, kp = (6, 32, 16), (6, 32, 16)
+    assert bench.adjoint_kernels(ka, kp, (84, 1896, 1000), 0, 4) == \
+        "k_adj_march<6, 0> + k_adj_tb<6, 32, 16, 1, 0>"
+    assert bench.adjoint_kernels((8, 64, 16), (8, 32, 16), (0, 252, 212), 3, 4) == \
+        "k_adj_tb<8, 64, 16, 0, 3> + k_adj_tb<8, 32, 16, 1, 3>"
+    assert bench.adjoint_kernels(ka, kp, (0, 0, 88), 0, 4) == "k_adj_tb<6, 32, 16, 1, 0>"
+    assert bench.adjoint_kernels((0, 0, 0), (0, 0, 0), (0, 0, 0), 0, 4) == "k_adj_step<4>"
+    assert bench.adjoint_kernels((0, 0, 0), (0, 0, 0), (0, 0, 0), 0, 64) == "k_adj_step<0>"
+
+
 def _trace(tmp_path, rows):
     p = tmp_path / "k_kernel_trace.csv"
     with open(p, "w") as f:
@@ -100,6 +112,13 @@ def test_counter_tables_are_keyed_alike():
         assert "k_adj" in kname and tile_map in (0, 1) and len(sha) == 16
         assert rd > 0 and wr > 0
     assert len(bench.kernel_sources_sha()) == 16
+
+
+def test_counter_entries_can_be_reached():
+    # the entries carry the name the benchmark's own workload runs under
+    # (marches beside 6x32x16 PML tiles); their source hash decides the rest
+    name = bench.adjoint_kernels((6, 32, 16), (6, 32, 16), (252, 1, 1), 0, 64)
+    assert {key[:3] for key in bench.PMC_TRAFFIC} == {(name, 1, "c3")}
 
 
 def test_more_than_one_gpu_is_refused():

@@ -211,3 +211,15 @@ def test_marches_without_a_radial_layer(pml):
     tiles = sv.kernel_tiles()
     assert tiles["fwd"][0] >= 64 and tiles["adj"][0] >= 64
     c.run([slice(138, 150)])
+
+
+def test_order4_reports_the_tiles_of_its_blocks():
+    import paper_2005_00281_amd as P
+    print("[case] tile report, order 4", flush=True)
+    _dev()
+    w = workloads.tiny(nr=60, nz=200, nt=40)
+    sv = P.Survey(w.shots, (w.NRg, w.NZg), ckpt_every=20, order=4)
+    assert {(m, a) for m, a, _ in sv.kernel_tiles().values()} == {(0, 0)}  # one launch
+    assert sv.kernel_tiles()["adj"][2] > 0
+    sv.set_order4_blocks(0)
+    assert set(sv.kernel_tiles().values()) == {(0, 0, 0)}
