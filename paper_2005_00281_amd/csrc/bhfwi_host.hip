@@ -299,6 +299,26 @@ bool touches_pml(const ShotDev& S, Shape sh, int i0, int k0)
     return ihi >= S.nr || klo < S.pz || khi >= S.NZ - S.pz;
 }
 
+// Interior tiles of shape sh in the column from k0: those that start at radial rows
+// 0, TRE - 2T, ... and stay clear of every layer.
+int interior_tiles(const ShotDev& S, Shape sh, int k0)
+{
+    return touches_pml(S, sh, 0, k0) ? 0 : (S.nr - (sh.TRE - sh.T)) / (sh.TRE - 2 * sh.T) + 1;
+}
+
+// Whether n interior and p PML tiles run in one launch of the PML kernel (it
+// takes any tile): where they fit the GPU in one round of workgroups, one per
+// compute unit.  The interior and the PML launch would each leave most of the GPU
+// idle and run one after the other.  One shot of 148 x 552 cells, 1000 steps,
+// gradient with checkpoints, 6x32x16 tiles: 13.75 ms in two launches per block, 7.56
+// ms in one; beyond one round the interior kernel's second workgroup per
+// compute unit is worth more (340 x 2088 cells, 8x32x16: 19.6 ms against
+// 20.9 ms).
+bool one_launch(const bhfwi_ctx* c, Shape sh, Shape pml, int64_t n, int64_t p)
+{
+    return sh.T == pml.T && sh.TRE == pml.TRE && sh.W == pml.W && n > 0 && n + p <= c->ncu;
+}
+
 void build_tiles(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Shape pml,
                  TileSet* ts, bool overlap = false)
 {
@@ -325,10 +345,10 @@ void build_tiles(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Sh
         tl[0].clear();
         tl[1].clear();
         for (int k0 = 0; k0 < S.NZ; k0 += TZ) {
-            int i0 = 0;
-            if (!touches_pml(S, sh, 0, k0)) {
-                for (; i0 < S.NR && !touches_pml(S, sh, i0, k0); i0 += TR)
-                    tl[0].push_back(make_int4(k0, i0, i0, 0));
+            const int n = interior_tiles(S, sh, k0);
+            int i0 = n * TR;
+            if (n > 0) {
+                for (int j = 0; j < n; ++j) tl[0].push_back(make_int4(k0, j * TR, j * TR, 0));
                 const int last = S.nr - (sh.TRE - sh.T);  // highest start clear of the layer
                 if (overlap && i0 < S.NR && last > i0 - TR && last < i0 &&
                     !touches_pml(S, sh, last, k0)) {
@@ -349,16 +369,7 @@ void build_tiles(const bhfwi_ctx* c, const std::vector<int>& order, Shape sh, Sh
             }
         }
     }
-    // All tiles in one launch of the PML kernel (it takes any tile) where they
-    // fit the GPU in one round of workgroups, one per compute unit: the
-    // interior and the PML launch would each leave most of the GPU idle and run
-    // one after the other.  One shot of 148 x 552 cells, 1000 steps, gradient
-    // with checkpoints, 6x32x16 tiles: 13.75 ms in two launches per block, 7.56
-    // ms in one; beyond one round the interior kernel's second workgroup per
-    // compute unit is worth more (340 x 2088 cells, 8x32x16: 19.6 ms against
-    // 20.9 ms).
-    if (sh.T == pml.T && sh.TRE == pml.TRE && sh.W == pml.W && !ts->t[0].empty() &&
-        (int)(ts->t[0].size() + ts->t[1].size()) <= c->ncu) {
+    if (one_launch(c, sh, pml, (int64_t)ts->t[0].size(), (int64_t)ts->t[1].size())) {
         std::vector<std::pair<int, int4>> all;
         for (int q = 0; q < 2; ++q)
             for (size_t j = 0; j < ts->t[q].size(); ++j)
@@ -561,13 +572,23 @@ constexpr FwdCost kFwdCost[] = {{{6, 32, 16}, 2, 3.6, 7.1, 10.8, 9.2},
                                 {{8, 48, 16}, 2, 4.4, 10.8, 17.2, 14.9},
                                 {{8, 64, 16}, 1, 2.0, 17.1, 17.1, 11.2}};
 
-// Time of one block of shape f over every shot, from the tiles that would run.
-double block_time(const bhfwi_ctx* c, const std::vector<int>& order, const FwdCost& f)
+// Time of one block of shape f over every shot, from the tiles build_tiles makes.
+double block_time(const bhfwi_ctx* c, const FwdCost& f)
 {
-    TileSet ts;
-    build_tiles(c, order, f.sh, pml_shape(f.sh, false), &ts);
-    const int n = (int)ts.t[0].size(), p = (int)ts.t[1].size();
-    const int slots = f.per_cu * c->ncu, rest = n % slots;
+    const Shape pml = pml_shape(f.sh, false);
+    const int T = f.sh.T, TR = f.sh.TRE - 2 * T, TRp = pml.TRE - 2 * T;
+    int64_t n = 0, p = 0;
+    for (const ShotDev& S : c->sd)
+        for (int k0 = 0; k0 < S.NZ; k0 += 64 - 2 * T) {
+            const int m = interior_tiles(S, f.sh, k0);
+            n += m;
+            p += (std::max(0, S.NR - m * TR) + TRp - 1) / TRp;
+        }
+    if (one_launch(c, f.sh, pml, n, p)) {
+        p += n;
+        n = 0;
+    }
+    const int64_t slots = (int64_t)f.per_cu * c->ncu, rest = n % slots;
     return f.launch * ((n > 0) + (p > 0)) + f.full * (n / slots + (rest > c->ncu)) +
            f.half * (rest > 0 && rest <= c->ncu) + f.pml * ((p + c->ncu - 1) / c->ncu);
 }
@@ -588,11 +609,9 @@ void default_shapes(bhfwi_ctx* c)
     c->own_adj = Shape{6, 32, 16};
     c->own_fwd = Shape{8, 48, 16};
     if (!march_rows(c, 8)) {
-        std::vector<int> order(c->nshot);
-        for (int s = 0; s < c->nshot; ++s) order[s] = s;
         double best = 0;
         for (const FwdCost& f : kFwdCost) {
-            const double t = block_time(c, order, f) / f.sh.T;
+            const double t = block_time(c, f) / f.sh.T;
             if (!best || t < best) {
                 best = t;
                 c->own_fwd = f.sh;
