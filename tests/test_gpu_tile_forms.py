@@ -223,3 +223,33 @@ def test_order4_reports_the_tiles_of_its_blocks():
     assert sv.kernel_tiles()["adj"][2] > 0
     sv.set_order4_blocks(0)
     assert set(sv.kernel_tiles().values()) == {(0, 0, 0)}
+
+
+def test_graph_replays_of_the_marches_equal_eager_launches():
+    """The captured sequence of marches beside PML tiles on the forked stream,
+    replayed with eager work and synchronisations in between, gives the eager
+    launches' traces and accumulators bit for bit."""
+    print("[case] march graph replays", flush=True)
+    c = _Check(_batch([(150, 288)] * 300, 100), ())
+    out = {}
+    for graph in (0, 1):
+        sv = c.survey(use_graph=graph, **MID)
+        assert sv.kernel_tiles()["fwd"][0] >= 64 and sv.kernel_tiles()["adj"][0] >= 64
+        args = (c.lam, c.mu, c.rho, c.wav)
+        r = torch.randn(sv.sizes.trace_elems, device=sv.device,
+                        generator=torch.Generator(device=sv.device).manual_seed(4))
+        tr = torch.empty_like(r)
+        acc = torch.empty(sv.sizes.acc_elems, device=sv.device)
+        for rep in range(4 if graph else 1):
+            tr.fill_(float("nan"))
+            acc.fill_(float("nan"))
+            sv.fwd_model(*args, store_ckpt=True, traces=tr)
+            sv.adjoint_model(*args, r, acc=acc)
+            torch.cuda.synchronize()
+            assert (c.lam * 2).sum().item() > 0  # unrelated eager work between replays
+            views = [v.clone() for v in sv.acc_views(acc)]
+            if not graph:
+                out["tr"], out["acc"] = tr.clone(), views
+            else:
+                assert torch.equal(tr, out["tr"]), rep
+                assert all(torch.equal(a, b) for a, b in zip(views, out["acc"])), rep
