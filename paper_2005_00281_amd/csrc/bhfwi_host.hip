@@ -408,12 +408,15 @@ constexpr int kFwdMarch = 8, kAdjMarch = 6;
 // where the LDS tiles run.  A wave issues a vector instruction every other
 // slot of its SIMD, so the marches need two waves per SIMD (8 per compute
 // unit) to keep the GPU busy, and a tile of R rows takes R + 2T march steps:
-// R minimises the number of rounds of that many waves times R + 2T.  Below 64
-// rows the fill (2T of R + 2T steps) costs more than the LDS tiles' halo, and
-// a survey that needs shorter tiles to fill the GPU keeps the LDS tiles
+// R minimises the number of rounds of that many waves times R + 2T.  With less
+// than 64 rows for R the fill (2T of R + 2T steps) costs more than the LDS tiles'
+// halo, and a survey that needs them to fill the GPU keeps the LDS tiles
 // (measured, gradient of 400 steps: 4 shots of 276 x 4136 cells 31.3 ms in LDS
 // tiles, 34.5 ms in 48-row marches; 8 shots 63.9 against 55.5 ms in 84-row
-// marches).  Planes and model windows are addressed by 32-bit byte offsets.
+// marches).  R is the most: a column is cut into equal tiles, which can be shorter
+// (43 to 63 rows: forwards 1.07 to 1.29 times as fast as in LDS tiles, six-step
+// adjoints 0.93 to 1.09).  Planes and model windows are addressed by 32-bit byte
+// offsets.
 int march_rows(const bhfwi_ctx* c, int T)
 {
     if (!(T == 4 || T == 6 || T == 8)) return 0;
